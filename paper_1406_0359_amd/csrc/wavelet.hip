@@ -10,7 +10,11 @@
 // All wavelet bases run in the same launch; a level is one launch of 2D tiles (both axes
 // through LDS).  The finest synthesis level sums every basis (and the Dirac block) per
 // output tile and writes the image once.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
+#include "lds_limit.h"
 #include "partials.h"
 
 namespace purify {
@@ -24,597 +28,534 @@ struct WavArgs {
     int dirac_block;      // -1 if no Dirac basis
 };
 
-// filters layout: [basis][0..15] = h, [basis][16..31] = g.  Kernels stage a basis' taps in
-// LDS (lanes index them by output parity, which a register array cannot serve).
+// Every level is one launch of 2D tiles, both axes through LDS.  The filters' lengths are
+// template arguments of the two filtering steps and a workgroup's taps sit in scalar registers,
+// so a step is a straight run of multiply-adds; each thread filters P adjacent positions, whose
+// inputs overlap: 2P + F - 2 values read from LDS give 2P outputs of F taps.  (With a runtime
+// filter length and one position a thread, three LDS reads fed four multiply-adds.)
+//
+// Tile geometry: TP0 x TP1 positions (2 TP0 x 2 TP1 image samples).  The first step filters
+// axis 1, a thread per P1 positions of a window row; the second axis 0, a thread per P0
+// positions of a column, its lanes along the row so that loads and stores are contiguous.
+template <int TP0_, int TP1_, int P1_, int P0_, int NT_>
+struct Geo {
+    static constexpr int TP0 = TP0_, TP1 = TP1_, P1 = P1_, P0 = P0_, NT = NT_;
+    static constexpr int HALO = MAX_TAPS - 2;
+    static constexpr int W0 = 2 * TP0 + HALO;       // window rows (at most)
+    static constexpr int W1 = 2 * TP1 + HALO;       // window columns (at most)
+    static constexpr int C0 = TP0 + HALO / 2;       // synthesis: window positions per subband
+    static constexpr int C1 = TP1 + HALO / 2;
+    static constexpr int SEG = TP1 / P1;            // first step: threads per window row
+    static constexpr int LW = W1 > 32 ? 64 : 32;    // lanes that load one window row
+    static constexpr int LR = NT / LW;              // rows loaded at a time
+    static constexpr int RB = (W0 + LR - 1) / LR;   // loads a thread
+    // LDS strides.  Analysis windows keep pad elements after every 8 (a thread's P1 = 4
+    // positions start 8 apart); synthesis windows hold the low and the high half of a row C1
+    // apart, at an odd stride.
+    template <typename T> static constexpr int pad() { return sizeof(T) == 4 ? 2 : 1; }
+    template <typename T> static constexpr int is() {
+        constexpr int w = W1 + pad<T>() * (W1 / 8);
+        constexpr int m = sizeof(T) == 4 ? 16 : 8, want = sizeof(T) == 4 ? 8 : 4;
+        return w + (want - w % m + m) % m;
+    }
+    static constexpr int WS = 2 * C1 + 1;
+    static constexpr int MS = 2 * TP1 + 2;
+    static_assert(W0 * SEG <= NT && 2 * TP1 * (TP0 / P0) <= NT, "one task a thread");
+    static_assert(W1 <= 64 && NT % 64 == 0, "one lane a window column");
+};
+// 32 x 32 samples.  (64 x 32 samples with 320 threads have less halo but fewer workgroups a CU to
+// hide the windows' loads behind: 4096^2 analysis 500 -> 678 us, synthesis 732 -> 991 us.)
+using GeoWav = Geo<16, 16, 4, 2, 256>;
+
+// Taps of one basis: lowpass h; highpass g[k] = (-1)^k h[F - 1 - k].
+template <typename T, int F>
+struct Taps {
+    T h[F];
+    __device__ __forceinline__ explicit Taps(const T* __restrict__ f) {
+#pragma unroll
+        for (int k = 0; k < F; ++k) h[k] = f[k];
+    }
+    __device__ __forceinline__ T lo(int k) const { return h[k]; }
+    __device__ __forceinline__ T hi(int k) const { return (k & 1) ? -h[F - 1 - k] : h[F - 1 - k]; }
+};
 
 __device__ __forceinline__ float fma_(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return fma(a, b, c); }
 
-// Row and column of a flattened tile index: i / d and i mod d for 0 <= i < 2^20 and
-// 1 <= d < 2^12 (every tile and window index here) from a float reciprocal taken once.  The
-// float quotient is within 1/4 of i / d, so its truncation is off by at most one, which one
-// remainder test corrects; a few instructions instead of an integer division, in kernels
-// whose arithmetic, not memory, sets their time.
-struct SmallDiv {
-    int d;
-    float rd;
-    __device__ explicit SmallDiv(int d_) : d(d_), rd(__builtin_amdgcn_rcpf((float)d_)) {}   // 1-ulp reciprocal
-    __device__ __forceinline__ int quot(int i, int& rem) const {
-        int q = (int)((float)i * rd);
-        int r = i - q * d;
-        if (r >= d) {
-            ++q;
-            r -= d;
-        } else if (r < 0) {
-            --q;
-            r += d;
-        }
-        rem = r;
-        return q;
-    }
-};
-
-// Global-to-LDS staging of `count` elements (element i read by ld(i) and stored by st(i, v),
-// count <= MAXE NTH): a thread issues the loads of all its elements before storing any, so
-// they are in flight together rather than one memory latency after another.
-template <typename V, int MAXE, int NTH, typename Ld, typename St>
-__device__ __forceinline__ void stage_batched(int count, int tid, Ld ld, St st) {
-    V v[MAXE];
-#pragma unroll
-    for (int k = 0; k < MAXE; ++k) {
-        const int i = tid + k * NTH;
-        if (i < count) v[k] = ld(i);
-    }
-#pragma unroll
-    for (int k = 0; k < MAXE; ++k) {
-        const int i = tid + k * NTH;
-        if (i < count) st(i, v[k]);
+// f(std::integral_constant<int, F>) for a filter length F = 2, 4, ..., 16 (uniform)
+template <typename Fn>
+__device__ __forceinline__ void with_flen(int F, Fn f) {
+    switch (F) {
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 8: f(std::integral_constant<int, 8>{}); break;
+        case 10: f(std::integral_constant<int, 10>{}); break;
+        case 12: f(std::integral_constant<int, 12>{}); break;
+        case 14: f(std::integral_constant<int, 14>{}); break;
+        default: f(std::integral_constant<int, 16>{}); break;
     }
 }
 
-// Every level is one launch of 2D tiles over all bases, both axes through LDS.  Each thread
-// computes output pairs that read the same inputs: the lowpass and highpass coefficient at
-// one position (analysis), or the even and odd sample from one window of coefficients
-// (synthesis), so every LDS read feeds two outputs.
-constexpr int AP = 16;                      // analysis tile: outputs per axis per subband (max)
-constexpr int AR = 2 * AP + MAX_TAPS - 2;   // analysis tile: input rows/cols needed (max, even)
-constexpr int SP = 32;                      // synthesis tile: outputs per axis (max)
-constexpr int SC = SP / 2 + MAX_TAPS / 2 - 1;   // synthesis window per axis per subband (max)
+// P adjacent positions of one axis: lo[p] = sum_k h[k] v[2p + k], hi[p] = sum_k g[k] v[2p + k]
+template <typename T, int F, int P>
+__device__ __forceinline__ void analyse(const cpx<T>* v, const Taps<T, F>& t, cpx<T>* lo, cpx<T>* hi) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        T lx = 0, ly = 0, hx = 0, hy = 0;
+#pragma unroll
+        for (int k = 0; k < F; ++k) {
+            const cpx<T> a = v[2 * p + k];
+            lx = fma_(t.lo(k), a.x, lx);
+            ly = fma_(t.lo(k), a.y, ly);
+            hx = fma_(t.hi(k), a.x, hx);
+            hy = fma_(t.hi(k), a.y, hy);
+        }
+        lo[p] = mk<T>(lx, ly);
+        hi[p] = mk<T>(hx, hy);
+    }
+}
 
-// One analysis level on a tile: coefficients at positions [ap ti1, ap ti1 + ap) x
-// [ap ti2, ...) of all four subbands of the Ls x Ls block (ap = min(AP, Ls/2)), from the
-// (2 ap + F - 2)^2 input window starting at (2 ap ti1, 2 ap ti2) (periodic).  Axis 1 is
-// filtered first, then axis 0.  Window rows are stored even samples first, then odd, so
-// lanes with consecutive outputs read consecutive LDS words.  src: the image (level 0,
-// shared by all bases, times `scale`; src_bstride = 0) or the previous level's LL blocks
-// (compact slots).  Detail subbands go to the alpha block; the LL subband goes to `llout`
-// (compact slots of (n/2)^2 per basis, row stride Ls/2), or into the alpha block at the
-// coarsest level (llout == null), so no launch reads what it writes.  blockIdx.z == nwav
-// copies the image into the Dirac block instead.
+// The transpose: sample pairs 2j, 2j + 1 from the coefficients j - t, t < F/2; lo and hi hold
+// P + F/2 - 1 coefficients from j_0 - (F/2 - 1) on.  Adds to even[p] and odd[p].
+template <typename T, int F, int P>
+__device__ __forceinline__ void synthesise(const cpx<T>* lo, const cpx<T>* hi, const Taps<T, F>& tp, cpx<T>* even,
+                                           cpx<T>* odd) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+        for (int t = 0; t < F / 2; ++t) {
+            const cpx<T> l = lo[p + F / 2 - 1 - t], h = hi[p + F / 2 - 1 - t];
+            even[p].x = fma_(tp.lo(2 * t), l.x, even[p].x);
+            even[p].y = fma_(tp.lo(2 * t), l.y, even[p].y);
+            even[p].x = fma_(tp.hi(2 * t), h.x, even[p].x);
+            even[p].y = fma_(tp.hi(2 * t), h.y, even[p].y);
+            odd[p].x = fma_(tp.lo(2 * t + 1), l.x, odd[p].x);
+            odd[p].y = fma_(tp.lo(2 * t + 1), l.y, odd[p].y);
+            odd[p].x = fma_(tp.hi(2 * t + 1), h.x, odd[p].x);
+            odd[p].y = fma_(tp.hi(2 * t + 1), h.y, odd[p].y);
+        }
+    }
+}
+
+// One analysis level on a tile.  src: the image (finest level, shared by all bases, times
+// `scale`; src_bstride = 0) or the previous level's LL blocks (compact slots).  Detail subbands
+// go to the alpha block; the LL subband to `llout` (compact slots of (n/2)^2 per basis, row
+// stride Ls/2), or into the alpha block at the coarsest level (llout == null), so no launch
+// reads what it writes.  Where Ls/2 is smaller than a tile the window repeats periodically and
+// the surplus positions are not written.
+// One basis a workgroup (blockIdx.y), the Dirac block a workgroup of its own (blockIdx.y ==
+// nwav), or with ALL every basis and the Dirac block in turn: a thread's inputs of a window row
+// then stay in registers for all bases, and `mid` is double-buffered in the window's LDS, so a
+// basis costs one barrier.
 // XHAT (finest level only): the image is x + a p with a the CG step length from xa's partial
 // sums, formed as the window is read.
-template <typename T, bool XHAT>
-__global__ void __launch_bounds__(256)
-k_wav_fwd_level(const cpx<T>* __restrict__ src, size_t src_bstride, int src_ld, cpx<T>* __restrict__ alpha,
-                cpx<T>* __restrict__ llout, const T* __restrict__ filt, WavArgs A, int Ls, T scale,
-                XhatArgs<T> xa) {
-    constexpr int IS = AR + 1, MS = 2 * AP + 1;
-    __shared__ cpx<T> in[AR * IS];
-    __shared__ cpx<T> mid[AR * MS];
-    __shared__ T tp[2 * MAX_TAPS];
+// Bound: large images by the write of the coefficients (4096^2, nine bases and five levels: 1.34
+// GB in and out, 275 us at the copy rate of 4.9 TB/s) beside about as much arithmetic; small ones
+// by the latency of a launch's window, taps and two steps.  With register-blocked steps of fixed
+// filter length 4096^2 FP32 takes 508 us (644 before), 1024^2 43 (63), 256^2 FP64 19 (32).
+template <typename T, typename G, bool ALL, bool XHAT>
+__global__ void __launch_bounds__(G::NT)
+k_wav_fwd(const cpx<T>* __restrict__ src, size_t src_bstride, cpx<T>* __restrict__ alpha,
+          cpx<T>* __restrict__ llout, const T* __restrict__ filt, WavArgs A, int Ls, T scale, XhatArgs<T> xa) {
+    constexpr int IS = G::template is<T>(), PADE = G::template pad<T>(), MS = G::MS, P1 = G::P1, P0 = G::P0;
+    constexpr int IN = G::W0 * IS, MID = G::W0 * MS;
+    static_assert(2 * P1 == 8, "window pads follow the segments");
+    __shared__ __attribute__((aligned(16))) cpx<T> sm[ALL ? (IN > 2 * MID ? IN : 2 * MID) : IN + MID];
     const int n = A.n;
     const size_t N = (size_t)n * n;
     const int half = Ls >> 1;
-    const int ap = half < AP ? half : AP;
-    const int tiles = half / ap;
-    const int ti1 = blockIdx.x / tiles, ti2 = blockIdx.x % tiles;
-    const int r0 = 2 * ap * ti1, c0 = 2 * ap * ti2;
-    const int z = blockIdx.z;
-    T xs = 0;
-    if constexpr (XHAT) xs = cg_alpha<T>(xa.rho_part, xa.rho_count, xa.pq_part, xa.pq_count);
-    // image element at offset o (x + a p with XHAT)
-    auto img = [&](size_t o) {
-        if constexpr (XHAT) return src[o] + xs * xa.p[o];
-        else return src[o];
-    };
-    if (z == A.nwav) {
-        cpx<T>* d = alpha + (size_t)A.dirac_block * N;
-        const SmallDiv d2a(2 * ap);
-        auto at = [&](int i) {
-            int c;
-            const int r = d2a.quot(i, c);
-            return (size_t)(r0 + r) * n + c0 + c;
-        };
-        stage_batched<cpx<T>, 4 * AP * AP / 256, 256>(
-            4 * ap * ap, threadIdx.x, [&](int i) { return img(at(i)); },
-            [&](int i, cpx<T> v) { d[at(i)] = scale * v; });
-        return;
-    }
-    const size_t blk = (size_t)A.block[z] * N;
-    const cpx<T>* s = src + (size_t)z * src_bstride;
-    const int F = A.flen[z];
-    const int R = 2 * ap + F - 2, RH = R >> 1;
-    const SmallDiv dR(R), da(ap), d2a(2 * ap);
-    // the taps and the window (R <= AR) are loaded together, then stored to LDS
-    const T tap = threadIdx.x < 2 * MAX_TAPS ? filt[z * 2 * MAX_TAPS + threadIdx.x] : (T)0;
-    stage_batched<cpx<T>, (AR * AR + 255) / 256, 256>(
-        R * R, threadIdx.x,
-        [&](int i) {
-            int b;
-            const int a = dR.quot(i, b);
-            const size_t o = (size_t)((r0 + a) & (Ls - 1)) * src_ld + ((c0 + b) & (Ls - 1));
-            if constexpr (XHAT) return img(o);
-            else return s[o];
-        },
-        [&](int i, cpx<T> v) {
-            int b;
-            const int a = dR.quot(i, b);
-            in[a * IS + (b & 1) * RH + (b >> 1)] = v;
-        });
-    if (threadIdx.x < 2 * MAX_TAPS) tp[threadIdx.x] = tap;
-    __syncthreads();
-    // axis 1: window row a, position oi -> mid[a][oi] (low), mid[a][ap + oi] (high)
-    for (int i = threadIdx.x; i < R * ap; i += 256) {
-        int oi;
-        const int a = da.quot(i, oi);
-        const cpx<T>* row = in + a * IS + oi;
-        T lx = 0, ly = 0, hx = 0, hy = 0;
+    const int tiles1 = half > G::TP1 ? half / G::TP1 : 1;
+    const int ti0 = blockIdx.x / tiles1, ti1 = blockIdx.x % tiles1;
+    const int r0 = 2 * G::TP0 * ti0, c0 = 2 * G::TP1 * ti1;
+    const int z0 = ALL ? 0 : (int)blockIdx.y;
+    const bool dirac = ALL ? A.dirac_block >= 0 : z0 == A.nwav;
+    // the window's extent: the basis' filter (ALL: the longest, the last basis'), or the tile
+    // itself for the Dirac block
+    const int F0 = ALL ? A.flen[A.nwav - 1] : (dirac ? 2 : A.flen[z0]);
+    const int R0 = 2 * G::TP0 + F0 - 2, R1 = 2 * G::TP1 + F0 - 2;
+    {   // lane = column, all of a thread's rows in flight before any is stored
+        const cpx<T>* s = src + (ALL || dirac ? 0 : (size_t)z0 * src_bstride);
+        const int b = threadIdx.x % G::LW, a0 = threadIdx.x / G::LW;
+        const size_t co = (size_t)((c0 + b) & (Ls - 1));
+        T xs = 0;
+        if constexpr (XHAT) xs = cg_alpha<T>(xa.rho_part, xa.rho_count, xa.pq_part, xa.pq_count);
+        (void)xs;
+        if (b < R1) {
+            cpx<T> v[G::RB], pv[XHAT ? G::RB : 1];
 #pragma unroll
-        for (int k = 0; k < MAX_TAPS; ++k) {
-            if (k >= F) break;
-            const cpx<T> v = row[(k & 1) * RH + (k >> 1)];
-            const T h = tp[k], g = tp[MAX_TAPS + k];
-            lx += h * v.x;
-            ly += h * v.y;
-            hx += g * v.x;
-            hy += g * v.y;
-        }
-        mid[a * MS + oi] = mk<T>(lx, ly);
-        mid[a * MS + ap + oi] = mk<T>(hx, hy);
-    }
-    __syncthreads();
-    // axis 0: position oi, column o1 (low | high along axis 1) -> both axis-0 subbands
-    for (int i = threadIdx.x; i < 2 * ap * ap; i += 256) {
-        int o1;
-        const int oi = d2a.quot(i, o1);
-        const cpx<T>* col = mid + 2 * oi * MS + o1;
-        T lx = 0, ly = 0, hx = 0, hy = 0;
+            for (int k = 0; k < G::RB; ++k) {
+                // beyond the window: its last row again (a condition here would make the
+                // compiler wait for each load in a block of its own)
+                const int a = min(a0 + k * G::LR, R0 - 1);
+                const size_t o = (size_t)((r0 + a) & (Ls - 1)) * Ls + co;
+                v[k] = s[o];
+                if constexpr (XHAT) pv[k] = xa.p[o];
+            }
+            (void)pv;
 #pragma unroll
-        for (int k = 0; k < MAX_TAPS; ++k) {
-            if (k >= F) break;
-            const cpx<T> v = col[k * MS];
-            const T h = tp[k], g = tp[MAX_TAPS + k];
-            lx += h * v.x;
-            ly += h * v.y;
-            hx += g * v.x;
-            hy += g * v.y;
+            for (int k = 0; k < G::RB; ++k) {
+                const int a = min(a0 + k * G::LR, R0 - 1);
+                if constexpr (XHAT) v[k] = v[k] + xs * pv[k];
+                sm[a * IS + b + PADE * (b >> 3)] = v[k];
+            }
         }
-        const int row = ap * ti1 + oi;
-        const int cl = (o1 >= ap ? half + o1 - ap : o1) + ap * ti2;
-        if (o1 < ap && llout) llout[(size_t)z * (N / 4) + (size_t)row * half + cl] = mk<T>(scale * lx, scale * ly);
-        else alpha[blk + (size_t)row * n + cl] = mk<T>(scale * lx, scale * ly);
-        alpha[blk + (size_t)(half + row) * n + cl] = mk<T>(scale * hx, scale * hy);
-    }
-}
-
-// The finest analysis level of every basis at once: all bases read the same image window,
-// so a workgroup loads the (2 AP + Fmax - 2)^2 window of its tile once (polyphase rows, as
-// above) and runs each basis' two axis passes on it in turn, instead of each basis' own
-// workgroup re-reading the image.  The Dirac block is the scaled tile of the image.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_wav_fwd_level0_all(const cpx<T>* __restrict__ x, cpx<T>* __restrict__ alpha, cpx<T>* __restrict__ llout,
-                     const T* __restrict__ filt, WavArgs A, T scale, int Fmax) {
-    constexpr int IS = AR + 1, MS = 2 * AP + 1;
-    __shared__ cpx<T> in[AR * IS];
-    __shared__ cpx<T> mid[AR * MS];
-    __shared__ T tp[MAX_WAV][2 * MAX_TAPS];
-    const int n = A.n, Ls = n;
-    const size_t N = (size_t)n * n;
-    const int half = Ls >> 1;
-    const int tiles = half / AP;
-    const int ti1 = blockIdx.x / tiles, ti2 = blockIdx.x % tiles;
-    const int r0 = 2 * AP * ti1, c0 = 2 * AP * ti2;
-    const int R = 2 * AP + Fmax - 2, RH = R >> 1;
-    const SmallDiv dR(R);
-    // the taps of every basis (at most 256 values) and the window are loaded together
-    const T tap = threadIdx.x < A.nwav * 2 * MAX_TAPS ? filt[threadIdx.x] : (T)0;
-    stage_batched<cpx<T>, (AR * AR + 255) / 256, 256>(
-        R * R, threadIdx.x,
-        [&](int i) {
-            int b;
-            const int a = dR.quot(i, b);
-            return x[(size_t)((r0 + a) & (Ls - 1)) * n + ((c0 + b) & (Ls - 1))];
-        },
-        [&](int i, cpx<T> v) {
-            int b;
-            const int a = dR.quot(i, b);
-            in[a * IS + (b & 1) * RH + (b >> 1)] = v;
-        });
-    if (threadIdx.x < A.nwav * 2 * MAX_TAPS) tp[threadIdx.x / (2 * MAX_TAPS)][threadIdx.x % (2 * MAX_TAPS)] = tap;
-    if (A.dirac_block >= 0) {
-        cpx<T>* d = alpha + (size_t)A.dirac_block * N;
-        auto at = [&](int i) { return (size_t)(r0 + i / (2 * AP)) * n + c0 + i % (2 * AP); };
-        stage_batched<cpx<T>, 4 * AP * AP / 256, 256>(
-            4 * AP * AP, threadIdx.x, [&](int i) { return x[at(i)]; },
-            [&](int i, cpx<T> v) { d[at(i)] = scale * v; });
     }
     __syncthreads();
-    for (int z = 0; z < A.nwav; ++z) {
-        const size_t blk = (size_t)A.block[z] * N;
+    if (dirac) {   // the tile's own samples
+        for (int i = threadIdx.x; i < 4 * G::TP0 * G::TP1; i += G::NT) {
+            const int a = i / (2 * G::TP1), b = i % (2 * G::TP1);
+            if (r0 + a < n && c0 + b < n)
+                alpha[(size_t)A.dirac_block * N + (size_t)(r0 + a) * n + c0 + b] = scale * sm[a * IS + b + PADE * (b >> 3)];
+        }
+        if constexpr (!ALL) return;
+    }
+    // first step's task: window row, P1 positions from seg P1
+    const int row = threadIdx.x / G::SEG, seg = threadIdx.x % G::SEG;
+    const cpx<T>* wrow = sm + row * IS + seg * (2 * P1 + PADE);
+    constexpr int NV = 2 * P1 + G::HALO;
+    cpx<T> v[NV];
+    if constexpr (ALL) {
+        if (row < R0) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[j] = wrow[j + PADE * (j >> 3)];   // beyond R1: not used
+        }
+        __syncthreads();   // the window is in registers: its LDS becomes `mid`
+    }
+    // second step's task: column (low | high along axis 1), P0 positions from g0 P0
+    const int col = threadIdx.x % (2 * G::TP1), g0 = threadIdx.x / (2 * G::TP1);
+    const int i1 = G::TP1 * ti1 + (col >= G::TP1 ? col - G::TP1 : col);
+    const bool two = g0 < G::TP0 / P0 && i1 < half;
+    const int z1 = ALL ? A.nwav : z0 + 1;
+    for (int z = z0; z < z1; ++z) {
+        cpx<T>* mid = ALL ? sm + (z & 1) * MID : sm + IN;
         const int F = A.flen[z];
-        const int Rz = 2 * AP + F - 2;   // this basis uses the window's first Rz rows / cols
-        const T* h = tp[z];
-        const T* g = h + MAX_TAPS;
-        for (int i = threadIdx.x; i < Rz * AP; i += 256) {
-            const int a = i / AP, oi = i - a * AP;
-            const cpx<T>* row = in + a * IS + oi;
-            T lx = 0, ly = 0, hx = 0, hy = 0;
+        const T* h = filt + z * 2 * MAX_TAPS;
+        if (row < 2 * G::TP0 + F - 2) {
+            with_flen(F, [&](auto f) {
+                constexpr int FL = decltype(f)::value;
+                const Taps<T, FL> t(h);
+                if constexpr (!ALL) {
 #pragma unroll
-            for (int k = 0; k < MAX_TAPS; ++k) {
-                if (k >= F) break;
-                const cpx<T> v = row[(k & 1) * RH + (k >> 1)];
-                lx += h[k] * v.x;
-                ly += h[k] * v.y;
-                hx += g[k] * v.x;
-                hy += g[k] * v.y;
-            }
-            mid[a * MS + oi] = mk<T>(lx, ly);
-            mid[a * MS + AP + oi] = mk<T>(hx, hy);
+                    for (int j = 0; j < 2 * P1 + FL - 2; ++j) v[j] = wrow[j + PADE * (j >> 3)];
+                }
+                cpx<T> lo[P1], hi[P1];
+                analyse<T, FL, P1>(v, t, lo, hi);
+#pragma unroll
+                for (int p = 0; p < P1; ++p) {
+                    mid[row * MS + seg * P1 + p] = lo[p];
+                    mid[row * MS + G::TP1 + seg * P1 + p] = hi[p];
+                }
+            });
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < 2 * AP * AP; i += 256) {
-            const int oi = i / (2 * AP), o1 = i - oi * (2 * AP);
-            const cpx<T>* col = mid + 2 * oi * MS + o1;
-            T lx = 0, ly = 0, hx = 0, hy = 0;
+        if (two) {
+            const size_t blk = (size_t)A.block[z] * N;
+            const int i0 = G::TP0 * ti0 + P0 * g0;
+            const int cl = col >= G::TP1 ? half + i1 : i1;
+            cpx<T>* al = alpha + blk + (size_t)i0 * n + cl;
+            cpx<T>* ah = al + (size_t)half * n;
+            const bool toll = col < G::TP1 && llout;
+            cpx<T>* ll = toll ? llout + (size_t)z * (N / 4) + (size_t)i0 * half + cl : al;
+            const size_t lld = toll ? half : n;
+            with_flen(F, [&](auto f) {
+                constexpr int FL = decltype(f)::value;
+                const Taps<T, FL> t(h);
+                cpx<T> u[2 * P0 + FL - 2], lo[P0], hi[P0];
 #pragma unroll
-            for (int k = 0; k < MAX_TAPS; ++k) {
-                if (k >= F) break;
-                const cpx<T> v = col[k * MS];
-                lx += h[k] * v.x;
-                ly += h[k] * v.y;
-                hx += g[k] * v.x;
-                hy += g[k] * v.y;
-            }
-            const int row = AP * ti1 + oi;
-            const int cl = (o1 >= AP ? half + o1 - AP : o1) + AP * ti2;
-            if (o1 < AP && llout) llout[(size_t)z * (N / 4) + (size_t)row * half + cl] = mk<T>(scale * lx, scale * ly);
-            else alpha[blk + (size_t)row * n + cl] = mk<T>(scale * lx, scale * ly);
-            alpha[blk + (size_t)(half + row) * n + cl] = mk<T>(scale * hx, scale * hy);
+                for (int j = 0; j < 2 * P0 + FL - 2; ++j) u[j] = mid[(2 * P0 * g0 + j) * MS + col];
+                analyse<T, FL, P0>(u, t, lo, hi);
+#pragma unroll
+                for (int p = 0; p < P0; ++p) {
+                    if (i0 + p < half) {
+                        ll[p * lld] = scale * lo[p];
+                        ah[(size_t)p * n] = scale * hi[p];
+                    }
+                }
+            });
         }
-        __syncthreads();
     }
 }
 
-// Synthesis of one level on a po x po output tile (po = min(SP, Ls)) of one basis: the
-// window of the four subbands the tile reaches (po/2 + F/2 - 1 positions per axis per
-// subband, periodic) goes into `in`, axis 0 is undone into `mid`, then axis 1; the thread's
-// outputs (pairs of adjacent samples along axis 1) are returned through `emit`.
-// Window layout: rows [0, C) lowpass and [C, 2C) highpass along axis 0, columns likewise.
-// synth_tile loads the window and runs synth_axis0 and synth_axis1; the finest-level kernel
-// that prefetches the next basis uses synth_load (the window into registers) and
-// synth_store (registers into `in`) instead.
-template <typename T, int NTH, int CMAX>
+// Synthesis of one level on a tile of 2 TP0 x 2 TP1 samples of one basis: the window of the four
+// subbands the tile reaches (TP + F/2 - 1 positions per axis per subband, periodic) goes into
+// `in` (rows [0, C0) low and [C0, 2 C0) high along axis 0 for the filter's own C0 = TP0 + F/2 - 1;
+// columns low at 0 and high at G::C1), axis 1 is undone into `mid` (high rows at G::C0), then
+// axis 0.
+template <typename T, typename G>
 struct SynthWin {
-    static constexpr int WS = 2 * CMAX + 1;   // LDS row stride of `in` and `mid`
-    static constexpr int E = (4 * CMAX * CMAX + NTH - 1) / NTH;   // window elements a thread
-    cpx<T> v[E];
-    T tap;
+    T x[G::RB], y[G::RB];
 };
 
-template <typename T, int NTH, int CMAX>
-__device__ __forceinline__ void synth_load(SynthWin<T, NTH, CMAX>& w, const cpx<T>* __restrict__ alpha, size_t blk,
-                                           const cpx<T>* __restrict__ lls, int lld, int n, int half, int po,
-                                           int m0, int m1, int F, const T* __restrict__ ftaps, int tid) {
-    const int C = po / 2 + F / 2 - 1;
-    const SmallDiv d2c(2 * C);
+// a thread's window elements (lane = window column) into registers
+template <typename T, typename G>
+__device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __restrict__ ab,
+                                           const cpx<T>* __restrict__ lls, int lld, int n, int half, int m0, int m1,
+                                           int F, int tid) {
+    const int C0 = G::TP0 + F / 2 - 1, C1 = G::TP1 + F / 2 - 1;
     const int s0 = m0 / 2 - F / 2 + 1, s1 = m1 / 2 - F / 2 + 1;   // first window index
-    w.tap = tid < 2 * MAX_TAPS ? ftaps[tid] : (T)0;
+    const int b = tid % G::LW, a0 = tid / G::LW;
+    const bool h1 = b >= C1;
+    const int i1 = (s1 + (h1 ? b - C1 : b)) & (half - 1);
+    // low rows: the LL block or the axis-1 detail; high rows: the two other details
+    const cpx<T>* lowp = h1 ? ab + half + i1 : lls + i1;
+    const int lowld = h1 ? n : lld;
+    const cpx<T>* highp = ab + (size_t)half * n + (h1 ? half + i1 : i1);
 #pragma unroll
-    for (int k = 0; k < SynthWin<T, NTH, CMAX>::E; ++k) {
-        const int i = tid + k * NTH;
-        if (i < 4 * C * C) {
-            int v;
-            const int u = d2c.quot(i, v);
-            const bool h0 = u >= C, h1 = v >= C;
-            const int i0 = (s0 + (h0 ? u - C : u)) & (half - 1), i1 = (s1 + (h1 ? v - C : v)) & (half - 1);
-            w.v[k] = (!h0 && !h1) ? lls[(size_t)i0 * lld + i1]
-                                  : alpha[blk + (size_t)(i0 + (h0 ? half : 0)) * n + i1 + (h1 ? half : 0)];
-        }
+    for (int k = 0; k < G::RB; ++k) {
+        const int u = min(a0 + k * G::LR, 2 * C0 - 1);   // as in k_wav_fwd
+        const cpx<T>* q = u < C0 ? lowp + (size_t)((s0 + u) & (half - 1)) * lowld
+                                 : highp + (size_t)((s0 + u - C0) & (half - 1)) * n;
+        const cpx<T> c = *q;
+        w.x[k] = c.x;
+        w.y[k] = c.y;
     }
 }
 
-template <typename T, int NTH, int CMAX>
-__device__ __forceinline__ void synth_store(const SynthWin<T, NTH, CMAX>& w, int po, int F, T* tp, cpx<T>* in,
-                                            int tid) {
-    constexpr int WS = SynthWin<T, NTH, CMAX>::WS;
-    const int C = po / 2 + F / 2 - 1;
-    const SmallDiv d2c(2 * C);
+template <typename T, typename G>
+__device__ __forceinline__ void synth_store(const SynthWin<T, G>& w, int F, cpx<T>* in, int tid) {
+    const int C0 = G::TP0 + F / 2 - 1, C1 = G::TP1 + F / 2 - 1;
+    const int b = tid % G::LW, a0 = tid / G::LW;
+    const int c = b >= C1 ? G::C1 + b - C1 : b;
+    if (b >= 2 * C1) return;
 #pragma unroll
-    for (int k = 0; k < SynthWin<T, NTH, CMAX>::E; ++k) {
-        const int i = tid + k * NTH;
-        if (i < 4 * C * C) {
-            int v;
-            const int u = d2c.quot(i, v);
-            in[u * WS + v] = w.v[k];
-        }
-    }
-    if (tid < 2 * MAX_TAPS) tp[tid] = w.tap;
+    for (int k = 0; k < G::RB; ++k) in[min(a0 + k * G::LR, 2 * C0 - 1) * G::WS + c] = mk<T>(w.x[k], w.y[k]);
 }
 
-// undo axis 0: output rows 2j, 2j+1 (j = m0/2 + jr) for every window column v
-template <typename T, int NTH, int CMAX>
-__device__ __forceinline__ void synth_axis0(int po, int F, const T* tp, const cpx<T>* in, cpx<T>* mid, int tid) {
-    constexpr int WS = SynthWin<T, NTH, CMAX>::WS;
-    const int C = po / 2 + F / 2 - 1;
-    const int hp = po / 2;
-    const SmallDiv d2c(2 * C);
-    for (int i = tid; i < hp * 2 * C; i += NTH) {
-        int v;
-        const int jr = d2c.quot(i, v);
-        T ex = 0, ey = 0, ox = 0, oy = 0;
+// undo axis 1: a thread per P1 sample pairs of a window row.  INPLACE: `mid` reuses `in`'s LDS
+// (a barrier of the whole workgroup between the reads and the writes).
+template <typename T, typename G, bool INPLACE>
+__device__ __forceinline__ void synth_axis1(int F, const T* __restrict__ h, const cpx<T>* in, cpx<T>* mid, int tid,
+                                            bool active) {
+    constexpr int P1 = G::P1;
+    const int u = tid / G::SEG, seg = tid % G::SEG;
+    const int C0 = G::TP0 + F / 2 - 1;
+    const bool on = active && u < 2 * C0;
+    constexpr int NV = P1 + MAX_TAPS / 2 - 1;
+    cpx<T> lo[NV], hi[NV];
+    if (on) {
 #pragma unroll
-        for (int t = 0; t < MAX_TAPS / 2; ++t) {
-            if (2 * t >= F) break;
-            const int u = jr + F / 2 - 1 - t;   // window row of index j - t
-            const cpx<T> lo = in[u * WS + v], hv = in[(C + u) * WS + v];
-            const T he = tp[2 * t], ge = tp[MAX_TAPS + 2 * t];
-            const T ho = tp[2 * t + 1], go = tp[MAX_TAPS + 2 * t + 1];
-            // one fused multiply-add a product (the sum of the pair first costs a multiply,
-            // an FMA and an add)
-            ex = fma_(he, lo.x, ex);
-            ex = fma_(ge, hv.x, ex);
-            ey = fma_(he, lo.y, ey);
-            ey = fma_(ge, hv.y, ey);
-            ox = fma_(ho, lo.x, ox);
-            ox = fma_(go, hv.x, ox);
-            oy = fma_(ho, lo.y, oy);
-            oy = fma_(go, hv.y, oy);
+        for (int j = 0; j < NV; ++j) {
+            if (j < P1 + F / 2 - 1) {
+                lo[j] = in[u * G::WS + seg * P1 + j];
+                hi[j] = in[u * G::WS + G::C1 + seg * P1 + j];
+            }
         }
-        mid[(2 * jr) * WS + v] = mk<T>(ex, ey);
-        mid[(2 * jr + 1) * WS + v] = mk<T>(ox, oy);
     }
-}
-
-// undo axis 1: row r, output columns 2j, 2j+1 (a thread's k-th pair is i = tid + k NTH;
-// the unrolled k is a compile-time index for the caller's accumulators)
-template <typename T, int NTH, int CMAX, typename Emit>
-__device__ __forceinline__ void synth_axis1(int po, int F, const T* tp, const cpx<T>* mid, int tid, Emit emit) {
-    constexpr int WS = SynthWin<T, NTH, CMAX>::WS;
-    const int C = po / 2 + F / 2 - 1;
-    const int hp = po / 2;
-    constexpr int PMAX = CMAX - MAX_TAPS / 2 + 1;          // largest po / 2
-    constexpr int KMAX = (2 * PMAX * PMAX + NTH - 1) / NTH;
-    const SmallDiv dh(hp);
+    if constexpr (INPLACE) __syncthreads();
+    if (on) {
+        with_flen(F, [&](auto f) {
+            const Taps<T, decltype(f)::value> t(h);
+            cpx<T> e[P1], o[P1];
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        const int i = tid + k * NTH;
-        if (i >= po * hp) break;
-        int jc;
-        const int r = dh.quot(i, jc);
-        T ex = 0, ey = 0, ox = 0, oy = 0;
+            for (int p = 0; p < P1; ++p) e[p] = o[p] = mk<T>(0, 0);
+            synthesise<T, decltype(f)::value, P1>(lo, hi, t, e, o);
+            cpx<T>* m = mid + (u < C0 ? u : G::C0 + u - C0) * G::MS + 2 * seg * P1;
 #pragma unroll
-        for (int t = 0; t < MAX_TAPS / 2; ++t) {
-            if (2 * t >= F) break;
-            const int v = jc + F / 2 - 1 - t;
-            const cpx<T> lo = mid[r * WS + v], hv = mid[r * WS + C + v];
-            const T he = tp[2 * t], ge = tp[MAX_TAPS + 2 * t];
-            const T ho = tp[2 * t + 1], go = tp[MAX_TAPS + 2 * t + 1];
-            // one fused multiply-add a product (the sum of the pair first costs a multiply,
-            // an FMA and an add)
-            ex = fma_(he, lo.x, ex);
-            ex = fma_(ge, hv.x, ex);
-            ey = fma_(he, lo.y, ey);
-            ey = fma_(ge, hv.y, ey);
-            ox = fma_(ho, lo.x, ox);
-            ox = fma_(go, hv.x, ox);
-            oy = fma_(ho, lo.y, oy);
-            oy = fma_(go, hv.y, oy);
-        }
-        emit(k, r, 2 * jc, mk<T>(ex, ey), mk<T>(ox, oy));
-    }
-}
-
-template <typename T, int NTH, int CMAX, typename Emit>
-__device__ __forceinline__ void synth_tile(const cpx<T>* __restrict__ alpha, size_t blk, const cpx<T>* __restrict__ lls,
-                                          int lld, int n, int half, int po, int m0, int m1, int F,
-                                          const T* __restrict__ ftaps, T* tp, cpx<T>* in, cpx<T>* mid, int tid,
-                                          Emit emit) {
-    constexpr int WS = SynthWin<T, NTH, CMAX>::WS;
-    const int C = po / 2 + F / 2 - 1;
-    const SmallDiv d2c(2 * C);
-    const int s0 = m0 / 2 - F / 2 + 1, s1 = m1 / 2 - F / 2 + 1;   // first window index
-    // the basis' taps (ftaps, into tp) and the window (C <= CMAX) are loaded together, then
-    // stored to LDS
-    const T tap = tid < 2 * MAX_TAPS ? ftaps[tid] : (T)0;
-    stage_batched<cpx<T>, (4 * CMAX * CMAX + NTH - 1) / NTH, NTH>(
-        4 * C * C, tid,
-        [&](int i) {
-            int v;
-            const int u = d2c.quot(i, v);
-            const bool h0 = u >= C, h1 = v >= C;
-            const int i0 = (s0 + (h0 ? u - C : u)) & (half - 1), i1 = (s1 + (h1 ? v - C : v)) & (half - 1);
-            return (!h0 && !h1) ? lls[(size_t)i0 * lld + i1]
-                                : alpha[blk + (size_t)(i0 + (h0 ? half : 0)) * n + i1 + (h1 ? half : 0)];
-        },
-        [&](int i, cpx<T> val) {
-            int v;
-            const int u = d2c.quot(i, v);
-            in[u * WS + v] = val;
+            for (int p = 0; p < P1; ++p) {
+                m[2 * p] = e[p];
+                m[2 * p + 1] = o[p];
+            }
         });
-    if (tid < 2 * MAX_TAPS) tp[tid] = tap;
-    __syncthreads();
-    synth_axis0<T, NTH, CMAX>(po, F, tp, in, mid, tid);
-    __syncthreads();
-    synth_axis1<T, NTH, CMAX>(po, F, tp, mid, tid, emit);
+    }
 }
 
-// One synthesis level (output side Ls, level >= 1) for every basis (blockIdx.z): the
+// undo axis 0: a thread per P0 sample pairs of a column (task col, g0), added to even and odd
+template <typename T, typename G>
+__device__ __forceinline__ void synth_axis0(int F, const T* __restrict__ h, const cpx<T>* mid, int col, int g0,
+                                            cpx<T>* even, cpx<T>* odd) {
+    with_flen(F, [&](auto f) {
+        constexpr int FL = decltype(f)::value, NV = G::P0 + FL / 2 - 1;
+        const Taps<T, FL> t(h);
+        cpx<T> lo[NV], hi[NV];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            lo[j] = mid[(g0 * G::P0 + j) * G::MS + col];
+            hi[j] = mid[(G::C0 + g0 * G::P0 + j) * G::MS + col];
+        }
+        synthesise<T, FL, G::P0>(lo, hi, t, even, odd);
+    });
+}
+
+// One synthesis level (output side Ls, level >= 1) for every basis (blockIdx.y): the
 // coarser LL comes from `llin` (compact slots of (n/2)^2 per basis) or, at the coarsest
 // level, from the alpha block; the result goes to `out` (compact slots, row stride Ls).
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, typename G>
+__global__ void __launch_bounds__(G::NT)
 k_wav_inv_level(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
                 cpx<T>* __restrict__ out, const T* __restrict__ filt, WavArgs A, int Ls) {
-    constexpr int WS = 2 * SC + 1;
-    __shared__ cpx<T> in[2 * SC * WS];
-    __shared__ cpx<T> mid[SP * WS];
-    __shared__ T tp[2 * MAX_TAPS];
+    __shared__ __attribute__((aligned(16))) cpx<T> in[G::W0 * G::WS];
+    __shared__ __attribute__((aligned(16))) cpx<T> mid[2 * G::C0 * G::MS];
     const int n = A.n;
     const size_t N = (size_t)n * n;
     const int half = Ls >> 1;
-    const int po = Ls < SP ? Ls : SP;
-    const int tiles = Ls / po;
-    const int m0 = po * (blockIdx.x / tiles), m1 = po * (blockIdx.x % tiles);
-    const int z = blockIdx.z;
-    const size_t blk = (size_t)A.block[z] * N;
-    const cpx<T>* lls = ll_from_alpha ? alpha + blk : llin + (size_t)z * (N / 4);
-    const int lld = ll_from_alpha ? n : half;
-    cpx<T>* o = out + (size_t)z * (N / 4);
-    synth_tile<T, 256, SC>(alpha, blk, lls, lld, n, half, po, m0, m1, A.flen[z], filt + z * 2 * MAX_TAPS, tp, in,
-                           mid, (int)threadIdx.x,
-                       [&](int, int r, int c, cpx<T> e, cpx<T> od) {
-                           o[(size_t)(m0 + r) * Ls + m1 + c] = e;
-                           o[(size_t)(m0 + r) * Ls + m1 + c + 1] = od;
-                       });
+    const int tiles1 = Ls > 2 * G::TP1 ? Ls / (2 * G::TP1) : 1;
+    const int m0 = 2 * G::TP0 * (blockIdx.x / tiles1), m1 = 2 * G::TP1 * (blockIdx.x % tiles1);
+    const int z = blockIdx.y, F = A.flen[z];
+    const T* h = filt + z * 2 * MAX_TAPS;
+    const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
+    const int tid = threadIdx.x;
+    {
+        SynthWin<T, G> w;
+        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
+                         m1, F, tid);
+        synth_store<T, G>(w, F, in, tid);
+    }
+    __syncthreads();
+    synth_axis1<T, G, false>(F, h, in, mid, tid, true);
+    __syncthreads();
+    const int col = tid % (2 * G::TP1), g0 = tid / (2 * G::TP1);
+    if (g0 >= G::TP0 / G::P0 || m1 + col >= Ls) return;
+    cpx<T> e[G::P0], o[G::P0];
+#pragma unroll
+    for (int p = 0; p < G::P0; ++p) e[p] = o[p] = mk<T>(0, 0);
+    synth_axis0<T, G>(F, h, mid, col, g0, e, o);
+    const int r = m0 + 2 * G::P0 * g0;
+    cpx<T>* d = out + (size_t)z * (N / 4) + (size_t)r * Ls + m1 + col;
+#pragma unroll
+    for (int p = 0; p < G::P0; ++p) {
+        if (r + 2 * p < Ls) {
+            d[(size_t)(2 * p) * Ls] = e[p];
+            d[(size_t)(2 * p + 1) * Ls] = o[p];
+        }
+    }
 }
 
-// Finest synthesis level: an FP x FP image tile sums every basis plus the Dirac block, times
-// `scale`.  NSLOT groups of 256 threads synthesise different bases concurrently and their
-// partial sums are added in slot order (a fixed order: deterministic).
-template <typename T, int FP, int NSLOT>
-__global__ void __launch_bounds__(256 * NSLOT)
+// Finest synthesis level of small images: a 16 x 16 tile, one group of 128 threads a basis, all
+// bases at once (a 256^2 image has one such tile a CU, so a basis after another would wait out
+// each window's latency in turn).  The groups' partial sums are added in basis order, with the
+// Dirac block, times `scale`.
+using GeoFinal = Geo<8, 8, 2, 2, 128>;
+
+template <typename T>
+__global__ void __launch_bounds__(128 * MAX_WAV)
 k_wav_inv_final(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
                 cpx<T>* __restrict__ x, const T* __restrict__ filt, WavArgs A, T scale) {
-    constexpr int CF = FP / 2 + MAX_TAPS / 2 - 1;
-    constexpr int WS = 2 * CF + 1;
-    constexpr int PAIRS = (FP * FP / 2 + 255) / 256;   // output pairs per thread
-    __shared__ cpx<T> in[NSLOT][2 * CF * WS];
-    __shared__ cpx<T> mid[NSLOT][FP * WS];
-    __shared__ T tp[NSLOT][2 * MAX_TAPS];
-    __shared__ cpx<T> part[NSLOT][FP * FP];
+    using G = GeoFinal;
+    constexpr int FP = 2 * G::TP0;
+    constexpr int IN = G::W0 * G::WS, MID = 2 * G::C0 * G::MS, SZ = IN > MID ? IN : MID;
+    static_assert(FP * FP <= SZ, "a partial tile fits in the basis' window");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int n = A.n;
     const size_t N = (size_t)n * n;
     const int half = n >> 1;
     const int tiles = n / FP;
     const int m0 = FP * (blockIdx.x / tiles), m1 = FP * (blockIdx.x % tiles);
-    const int slot = threadIdx.x >> 8, tid = threadIdx.x & 255;
-    // thread tid owns the output pairs i = tid + 256 k: row i / (FP/2), columns 2 (i % (FP/2)) + {0, 1}
-    cpx<T> acc0[PAIRS], acc1[PAIRS];
-#pragma unroll
-    for (int k = 0; k < PAIRS; ++k) acc0[k] = acc1[k] = mk<T>(0, 0);
-    const int rounds = (A.nwav + NSLOT - 1) / NSLOT;
-    for (int rd = 0; rd < rounds; ++rd) {
-        const int z = rd * NSLOT + slot;
-        const bool active = z < A.nwav;
-        const int zz = active ? z : 0;
-        const size_t blk = (size_t)A.block[zz] * N;
-        const cpx<T>* lls = ll_from_alpha ? alpha + blk : llin + (size_t)zz * (N / 4);
-        const int lld = ll_from_alpha ? n : half;
-        if (rd > 0) __syncthreads();
-        // inactive slots run on basis 0 and discard the result (keeps the barriers uniform)
-        synth_tile<T, 256, CF>(alpha, blk, lls, lld, n, half, FP, m0, m1, A.flen[zz], filt + zz * 2 * MAX_TAPS,
-                               tp[slot], in[slot], mid[slot], tid, [&](int k, int, int, cpx<T> e, cpx<T> od) {
-                                   if (active) {
-                                       acc0[k].x += e.x;
-                                       acc0[k].y += e.y;
-                                       acc1[k].x += od.x;
-                                       acc1[k].y += od.y;
-                                   }
-                               });
+    const int z = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), tid = threadIdx.x & 127;
+    cpx<T>* in = reinterpret_cast<cpx<T>*>(smem_raw) + z * SZ;
+    const int F = A.flen[z];
+    const T* h = filt + z * 2 * MAX_TAPS;
+    const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
+    {
+        SynthWin<T, G> w;
+        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
+                         m1, F, tid);
+        synth_store<T, G>(w, F, in, tid);
     }
+    // the tile's Dirac samples are read before the barriers
+    const int pix = threadIdx.x;
+    const size_t po = (size_t)(m0 + (pix / FP) % FP) * n + m1 + pix % FP;
+    cpx<T> dv = mk<T>(0, 0);
+    if (pix < FP * FP && A.dirac_block >= 0) dv = alpha[(size_t)A.dirac_block * N + po];
+    __syncthreads();
+    synth_axis1<T, G, true>(F, h, in, in, tid, true);
+    __syncthreads();
+    const int col = tid % FP, g0 = tid / FP;
+    cpx<T> e[G::P0], o[G::P0];
 #pragma unroll
-    for (int k = 0; k < PAIRS; ++k) {
-        const int i = tid + 256 * k;
-        if (i < FP * FP / 2) {
-            const int r = i / (FP / 2), c = 2 * (i % (FP / 2));
-            part[slot][r * FP + c] = acc0[k];
-            part[slot][r * FP + c + 1] = acc1[k];
+    for (int p = 0; p < G::P0; ++p) e[p] = o[p] = mk<T>(0, 0);
+    const bool on = g0 < G::TP0 / G::P0;
+    if (on) synth_axis0<T, G>(F, h, in, col, g0, e, o);
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int p = 0; p < G::P0; ++p) {
+            in[(2 * (g0 * G::P0 + p)) * FP + col] = e[p];
+            in[(2 * (g0 * G::P0 + p) + 1) * FP + col] = o[p];
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < FP * FP; i += 256 * NSLOT) {
-        const int r = i / FP, c = i % FP;
-        const size_t o = (size_t)(m0 + r) * n + m1 + c;
-        T sx = 0, sy = 0;
-        if (A.dirac_block >= 0) {
-            const cpx<T> d = alpha[(size_t)A.dirac_block * N + o];
-            sx = d.x;
-            sy = d.y;
+    const cpx<T>* all = reinterpret_cast<const cpx<T>*>(smem_raw);
+    for (int i = pix; i < FP * FP; i += blockDim.x) {
+        cpx<T> s = dv;
+        size_t oi = po;
+        if (i != pix) {   // fewer than two bases: a thread has a second pixel
+            oi = (size_t)(m0 + i / FP) * n + m1 + i % FP;
+            s = A.dirac_block >= 0 ? alpha[(size_t)A.dirac_block * N + oi] : mk<T>(0, 0);
         }
-#pragma unroll
-        for (int sl = 0; sl < NSLOT; ++sl) {
-            sx += part[sl][i].x;
-            sy += part[sl][i].y;
-        }
-        x[o] = mk<T>(scale * sx, scale * sy);
+        for (int b = 0; b < A.nwav; ++b) s = s + all[b * SZ + i];
+        x[oi] = scale * s;
     }
 }
 
-// Finest synthesis level, one basis at a time per 256-thread workgroup, with the next basis'
-// window loaded into registers while the current one is filtered: it is stored to `in` as
-// soon as axis 0 of the current basis has read `in` (the taps are double-buffered), so its
-// load latency hides behind the filtering.  Same arithmetic, in the same basis order, as
-// k_wav_inv_final with one slot.
-template <typename T, int FP>
-__global__ void __launch_bounds__(256)
+// Finest synthesis level of large images, one basis at a time per workgroup, with the next
+// basis' window loaded into registers while the current one is filtered and stored to `in` after
+// its second step, so the loads have both steps to arrive.  The sums over the bases stay in
+// registers.
+// Bound by the windows' loads (1.5 times the coefficients, the halos from L2): 1024^2 FP32 whole
+// synthesis 75 -> 58 us, 4096^2 789 -> 730 us, 1024^2 FP64 195 -> 91 us.
+template <typename T, typename G>
+__global__ void __launch_bounds__(G::NT)
 k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
                      cpx<T>* __restrict__ x, const T* __restrict__ filt, WavArgs A, T scale) {
-    constexpr int CF = FP / 2 + MAX_TAPS / 2 - 1;
-    constexpr int WS = 2 * CF + 1;
-    constexpr int PAIRS = (FP * FP / 2 + 255) / 256;   // output pairs per thread
-    __shared__ cpx<T> in[2 * CF * WS];
-    __shared__ cpx<T> mid[FP * WS];
-    __shared__ T tp[2][2 * MAX_TAPS];
+    __shared__ __attribute__((aligned(16))) cpx<T> in[G::W0 * G::WS];
+    __shared__ __attribute__((aligned(16))) cpx<T> mid[2 * G::C0 * G::MS];
     const int n = A.n;
     const size_t N = (size_t)n * n;
     const int half = n >> 1;
-    const int tiles = n / FP;
-    const int m0 = FP * (blockIdx.x / tiles), m1 = FP * (blockIdx.x % tiles);
+    const int tiles1 = n / (2 * G::TP1);
+    // each XCD takes a contiguous range of tiles, so that the windows' halos meet in one L2
+    // (1024^2 FP32 64 -> 58 us, FP64 98 -> 91 us; the analysis, which writes, lost 4% so)
+    const int bx = gridDim.x % 8 ? blockIdx.x : (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const int m0 = 2 * G::TP0 * (bx / tiles1), m1 = 2 * G::TP1 * (bx % tiles1);
     const int tid = threadIdx.x;
     const int lld = ll_from_alpha ? n : half;
-    auto blk_of = [&](int z) { return (size_t)A.block[z] * N; };
-    auto lls_of = [&](int z) { return ll_from_alpha ? alpha + blk_of(z) : llin + (size_t)z * (N / 4); };
-    cpx<T> acc0[PAIRS], acc1[PAIRS];
+    const int col = tid % (2 * G::TP1), g0 = tid / (2 * G::TP1);
+    const bool on = g0 < G::TP0 / G::P0;
+    cpx<T> e[G::P0], o[G::P0];
 #pragma unroll
-    for (int k = 0; k < PAIRS; ++k) acc0[k] = acc1[k] = mk<T>(0, 0);
-    SynthWin<T, 256, CF> w;
-    synth_load<T, 256, CF>(w, alpha, blk_of(0), lls_of(0), lld, n, half, FP, m0, m1, A.flen[0], filt, tid);
-    synth_store<T, 256, CF>(w, FP, A.flen[0], tp[0], in, tid);
+    for (int p = 0; p < G::P0; ++p) e[p] = o[p] = mk<T>(0, 0);
+    SynthWin<T, G> w;
+    auto load = [&](int z) {
+        const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
+        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), lld, n, half, m0, m1, A.flen[z], tid);
+    };
+    load(0);
+    synth_store<T, G>(w, A.flen[0], in, tid);
     __syncthreads();
     for (int z = 0; z < A.nwav; ++z) {
         const int F = A.flen[z];
+        const T* h = filt + z * 2 * MAX_TAPS;
         const bool more = z + 1 < A.nwav;
-        if (more)
-            synth_load<T, 256, CF>(w, alpha, blk_of(z + 1), lls_of(z + 1), lld, n, half, FP, m0, m1, A.flen[z + 1],
-                                   filt + (z + 1) * 2 * MAX_TAPS, tid);
-        synth_axis0<T, 256, CF>(FP, F, tp[z & 1], in, mid, tid);
+        if (more) load(z + 1);
+        synth_axis1<T, G, false>(F, h, in, mid, tid, true);
         __syncthreads();
-        if (more) synth_store<T, 256, CF>(w, FP, A.flen[z + 1], tp[(z + 1) & 1], in, tid);
-        synth_axis1<T, 256, CF>(FP, F, tp[z & 1], mid, tid, [&](int k, int, int, cpx<T> e, cpx<T> od) {
-            acc0[k].x += e.x;
-            acc0[k].y += e.y;
-            acc1[k].x += od.x;
-            acc1[k].y += od.y;
-        });
+        if (on) {
+            cpx<T> be[G::P0], bo[G::P0];   // this basis' sums, added once formed
+#pragma unroll
+            for (int p = 0; p < G::P0; ++p) be[p] = bo[p] = mk<T>(0, 0);
+            synth_axis0<T, G>(F, h, mid, col, g0, be, bo);
+#pragma unroll
+            for (int p = 0; p < G::P0; ++p) {
+                e[p] = e[p] + be[p];
+                o[p] = o[p] + bo[p];
+            }
+        }
+        if (more) synth_store<T, G>(w, A.flen[z + 1], in, tid);
         __syncthreads();
     }
-    // each thread adds the Dirac block to its own output pairs and writes them
+    if (!on) return;
+    const size_t off = (size_t)(m0 + 2 * G::P0 * g0) * n + m1 + col;
 #pragma unroll
-    for (int k = 0; k < PAIRS; ++k) {
-        const int i = tid + 256 * k;
-        if (i < FP * FP / 2) {
-            const int r = i / (FP / 2), c = 2 * (i % (FP / 2));
-            const size_t o = (size_t)(m0 + r) * n + m1 + c;
-            cpx<T> e = acc0[k], od = acc1[k];
-            if (A.dirac_block >= 0) {
-                const cpx<T>* d = alpha + (size_t)A.dirac_block * N + o;
-                e = e + d[0];
-                od = od + d[1];
-            }
-            x[o] = scale * e;
-            x[o + 1] = scale * od;
+    for (int p = 0; p < G::P0; ++p) {
+        const size_t a = off + (size_t)(2 * p) * n, b = a + n;
+        if (A.dirac_block >= 0) {
+            const cpx<T>* d = alpha + (size_t)A.dirac_block * N;
+            e[p] = e[p] + d[a];
+            o[p] = o[p] + d[b];
         }
+        x[a] = scale * e[p];
+        x[b] = scale * o[p];
     }
 }
 
@@ -640,12 +581,17 @@ WavArgs wav_args(const Plan& P) {
 
 }  // namespace
 
-// The finest level goes through k_wav_fwd_level (which can form x + alpha p) unless the
-// image is large enough for the one-pass kernel of all bases.
-bool psi_adj_takes_xhat(const Plan& P) {
-    if (P.nwav == 0) return false;
-    const int ap = std::min(AP, P.n / 2), tiles = (P.n / 2) / ap;
-    return !(ap == AP && tiles * tiles >= 1024);
+// The finest analysis level can form x + alpha p on small images, whose CG update it then
+// overlaps; on large ones reading p beside x would cost more than the update kernel's pass.
+bool psi_adj_takes_xhat(const Plan& P) { return P.nwav > 0 && P.n < 1024; }
+
+template <typename T, typename G, bool ALL, bool XHAT>
+void fwd_level(const Plan& P, const WavArgs& A, int groups, int Ls, const cpx<T>* src, size_t bstride, cpx<T>* alpha,
+               cpx<T>* llout, T scale, const XhatArgs<T>& xa, hipStream_t s) {
+    const int half = Ls / 2;
+    const dim3 g(std::max(1, half / G::TP0) * std::max(1, half / G::TP1), groups);
+    hipLaunchKernelGGL((k_wav_fwd<T, G, ALL, XHAT>), g, dim3(G::NT), 0, s, src, bstride, alpha, llout,
+                       (const T*)P.filters, A, Ls, scale, xa);
 }
 
 template <typename T>
@@ -660,35 +606,39 @@ void launch_psi_adj(const Plan& P, const cpx<T>* x, cpx<T>* alpha, hipStream_t s
                            alpha, scale, N);
         return;
     }
-    const T* filt = (const T*)P.filters;
-    const int ztot = P.nwav + (P.has_dirac ? 1 : 0);
+    const XhatArgs<T> none{};
     // LL ping-pong buffers, one (n/2)^2 slot per basis each
     cpx<T>* llb[2] = {(cpx<T>*)P.ws2, (cpx<T>*)P.ws2 + (size_t)P.nwav * (N / 4)};
     for (int lev = 0; lev < P.levels; ++lev) {
         const int Ls = P.n >> lev;
-        const int half = Ls / 2, ap = std::min(AP, half);
-        const int tiles = half / ap;
-        const dim3 g(tiles * tiles, 1, lev == 0 ? ztot : P.nwav);
         cpx<T>* llout = lev + 1 < P.levels ? llb[lev & 1] : nullptr;
+        if (lev > 0) {
+            fwd_level<T, GeoWav, false, false>(P, A, P.nwav, Ls, llb[(lev - 1) & 1], (size_t)(N / 4), alpha, llout,
+                                               (T)1, none, s);
+            continue;
+        }
         // large images: one pass over the image for all bases (small ones need the bases'
         // separate workgroups to fill the device)
-        if (lev == 0 && ap == AP && tiles * tiles >= 1024) {
-            int Fmax = 2;
-            for (int i = 0; i < P.nwav; ++i) Fmax = std::max(Fmax, A.flen[i]);
-            hipLaunchKernelGGL(k_wav_fwd_level0_all<T>, dim3(tiles * tiles), dim3(256), 0, s, x, alpha, llout,
-                               filt, A, scale, Fmax);
-        } else if (lev == 0 && xa) {
-            hipLaunchKernelGGL((k_wav_fwd_level<T, true>), g, dim3(256), 0, s, x, (size_t)0, P.n, alpha, llout,
-                               filt, A, Ls, scale, *xa);
-        } else if (lev == 0) {
-            hipLaunchKernelGGL((k_wav_fwd_level<T, false>), g, dim3(256), 0, s, x, (size_t)0, P.n, alpha, llout,
-                               filt, A, Ls, scale, XhatArgs<T>{});
-        } else {
-            hipLaunchKernelGGL((k_wav_fwd_level<T, false>), g, dim3(256), 0, s, (const cpx<T>*)llb[(lev - 1) & 1],
-                               (size_t)(N / 4), Ls, alpha, llout, filt, A, Ls, (T)1, XhatArgs<T>{});
-        }
-        if (lev == 0 && first_done) (void)hipEventRecord(first_done, s);
+        const int ztot = P.nwav + (P.has_dirac ? 1 : 0);
+        if (P.n >= 1024) fwd_level<T, GeoWav, true, false>(P, A, 1, Ls, x, 0, alpha, llout, scale, none, s);
+        else if (xa) fwd_level<T, GeoWav, false, true>(P, A, ztot, Ls, x, 0, alpha, llout, scale, *xa, s);
+        else fwd_level<T, GeoWav, false, false>(P, A, ztot, Ls, x, 0, alpha, llout, scale, none, s);
+        if (first_done) (void)hipEventRecord(first_done, s);
     }
+}
+
+template <typename T, typename G>
+void inv_level(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T>* in, int from_alpha, cpx<T>* out,
+               int Ls, hipStream_t s) {
+    const dim3 g(std::max(1, Ls / (2 * G::TP0)) * std::max(1, Ls / (2 * G::TP1)), P.nwav);
+    hipLaunchKernelGGL((k_wav_inv_level<T, G>), g, dim3(G::NT), 0, s, alpha, in, from_alpha, out,
+                       (const T*)P.filters, A, Ls);
+}
+template <typename T, typename G>
+void inv_final_pipe(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T>* in, int from_alpha, cpx<T>* x,
+                    T scale, hipStream_t s) {
+    hipLaunchKernelGGL((k_wav_inv_final_pipe<T, G>), dim3(P.N / (4 * G::TP0 * G::TP1)), dim3(G::NT), 0, s, alpha, in,
+                       from_alpha, x, (const T*)P.filters, A, scale);
 }
 
 template <typename T>
@@ -701,36 +651,30 @@ void launch_psi(const Plan& P, const cpx<T>* alpha, cpx<T>* x, hipStream_t s) {
                            alpha, x, scale, N);
         return;
     }
-    const T* filt = (const T*)P.filters;
     // LL ping-pong buffers, one (n/2)^2 slot per basis each
     cpx<T>* llb[2] = {(cpx<T>*)P.ws2, (cpx<T>*)P.ws2 + (size_t)P.nwav * (N / 4)};
     int cur = -1;   // buffer holding the current LL, -1: the alpha block (coarsest level)
     for (int lev = P.levels - 1; lev >= 1; --lev) {
         const int Ls = P.n >> lev;
-        const int po = std::min(SP, Ls);
-        const int tiles = Ls / po;
         const int dst = cur == 0 ? 1 : 0;
         const cpx<T>* in = cur < 0 ? alpha : llb[cur];
-        hipLaunchKernelGGL(k_wav_inv_level<T>, dim3(tiles * tiles, 1, P.nwav), dim3(256), 0, s, alpha, in,
-                           cur < 0 ? 1 : 0, llb[dst], filt, A, Ls);
+        inv_level<T, GeoWav>(P, A, alpha, in, cur < 0 ? 1 : 0, llb[dst], Ls, s);
         cur = dst;
     }
     const cpx<T>* in = cur < 0 ? alpha : llb[cur];
-    // FP32 on large images: 32 x 32 tiles (half the window overhead of 16 x 16), one basis
-    // at a time per 256-thread workgroup with the next basis' window prefetched, so five
-    // workgroups share a CU's LDS and loads overlap filtering (4096^2: 1321 -> 950 us for the
-    // whole synthesis against four bases at a time in one 1024-thread workgroup)
-    if constexpr (sizeof(T) == 4) {
-        if (P.n >= 512) {
-            const int tiles = P.n / 32;
-            hipLaunchKernelGGL((k_wav_inv_final_pipe<T, 32>), dim3(tiles * tiles), dim3(256), 0, s, alpha, in,
-                               cur < 0 ? 1 : 0, x, filt, A, scale);
-            return;
-        }
+    // from 512^2 on there are at least as many 32 x 32 tiles as CUs and one basis after another
+    // has the next one's window in flight (512^2 FP64 60 -> 39 us, FP32 52 -> 32 us)
+    if (P.n >= 512) {
+        inv_final_pipe<T, GeoWav>(P, A, alpha, in, cur < 0 ? 1 : 0, x, scale, s);
+        return;
     }
+    constexpr int SZ = std::max(GeoFinal::W0 * GeoFinal::WS, 2 * GeoFinal::C0 * GeoFinal::MS);
+    const size_t lds = (size_t)P.nwav * SZ * sizeof(cpx<T>);
+    auto f = k_wav_inv_final<T>;
+    set_lds_limit(f, lds);
     const int tiles = P.n / 16;
-    hipLaunchKernelGGL((k_wav_inv_final<T, 16, 4>), dim3(tiles * tiles), dim3(1024), 0, s, alpha, in,
-                       cur < 0 ? 1 : 0, x, filt, A, scale);
+    hipLaunchKernelGGL(f, dim3(tiles * tiles), dim3(128 * P.nwav), lds, s, alpha, in, cur < 0 ? 1 : 0, x,
+                       (const T*)P.filters, A, scale);
 }
 
 template void launch_psi_adj<float>(const Plan&, const cpx<float>*, cpx<float>*, hipStream_t,
