@@ -50,17 +50,32 @@ template <> struct KBDeg<float> { static constexpr int value = 9; };
 constexpr int KB_MAX_J = 16;
 constexpr int KB_MAX_COEF = KB_MAX_J * 18;
 
-// w[a] = psi(f + J/2 - 1 - a), a < J;  c: [a][k] coefficients, k = 0..DEG (device memory)
+// w[a] = psi(f + J/2 - 1 - a), a < J;  c: [a][k] coefficients, k = 0..DEG (device memory).
+// psi is even, so tap J - 1 - a at x is tap a at -x: with y = x^2, the pair is E(y) + x O(y) and
+// E(y) - x O(y) of tap a's even and odd coefficients, ten operations instead of eighteen.
 template <typename T, int J>
 __device__ __forceinline__ void kb_weights(const T* __restrict__ c, T f, T* w) {
-    constexpr int NC = KBDeg<T>::value + 1;
-    const T x = f - (T)0.5;
+    constexpr int DEG = KBDeg<T>::value, NC = DEG + 1, NP = (J + 1) / 2;
+    static_assert(DEG % 2 == 1, "as many even as odd coefficients");
+    const T x = f - (T)0.5, y = x * x;
+    T e[NP], o[NP];
 #pragma unroll
-    for (int a = 0; a < J; ++a) w[a] = c[a * NC + NC - 1];
+    for (int a = 0; a < NP; ++a) {
+        e[a] = c[a * NC + DEG - 1];
+        o[a] = c[a * NC + DEG];
+    }
 #pragma unroll
-    for (int k = NC - 2; k >= 0; --k) {
+    for (int k = DEG - 3; k >= 0; k -= 2) {
 #pragma unroll
-        for (int a = 0; a < J; ++a) w[a] = w[a] * x + c[a * NC + k];
+        for (int a = 0; a < NP; ++a) {
+            e[a] = e[a] * y + c[a * NC + k];
+            o[a] = o[a] * y + c[a * NC + k + 1];
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+        w[J - 1 - a] = e[a] - x * o[a];
+        w[a] = e[a] + x * o[a];
     }
 }
 

@@ -20,6 +20,22 @@ namespace purify {
 namespace {
 
 
+// CALL with J_ = P.J for the widths with kernels of their own (up to 8; unrolled taps and
+// margins of the width itself), J_ = 0 for wider ones, whose kernels loop over a runtime width
+// (512^2 FP32, J = 7, 180221 visibilities: G^T G 107 us by the runtime
+// kernel, 32 by its own).
+#define PURIFY_J_DISPATCH(J_VAR, CALL)                  \
+    switch (J_VAR) {                                    \
+        case 2: { constexpr int J_ = 2; CALL; } break;  \
+        case 3: { constexpr int J_ = 3; CALL; } break;  \
+        case 4: { constexpr int J_ = 4; CALL; } break;  \
+        case 5: { constexpr int J_ = 5; CALL; } break;  \
+        case 6: { constexpr int J_ = 6; CALL; } break;  \
+        case 7: { constexpr int J_ = 7; CALL; } break;  \
+        case 8: { constexpr int J_ = 8; CALL; } break;  \
+        default: { constexpr int J_ = 0; CALL; } break; \
+    }
+
 // Runtime-J variant of kb_weights (J <= 16), for the less common kernel widths.
 template <typename T>
 __device__ __noinline__ void kb_weights_any(const T* __restrict__ c, T f, T* w, int J) {
@@ -202,11 +218,11 @@ k_degrid_tiles(const cpx<T>* __restrict__ grid, cpx<T>* __restrict__ y, const in
             ax += wa[a] * rx;
             ay += wa[a] * ry;
         };
-        // FP64 and J = 8: two rows at a time, so the window reads of all J rows are not all
+        // FP64 and J >= 7: two rows at a time, so the window reads of all J rows are not all
         // held in registers at once (158 -> 65 VGPRs at J = 8, four workgroups a CU instead
         // of three: 4096^2 G 233 -> 220 us; FP64 256^2 4.0 -> 3.4 us); FP32 with J <= 6 keeps
         // the fully unrolled form (1024^2 G 26.8 against 30.0 us)
-        if constexpr (sizeof(T) == 8 || J == 8) {
+        if constexpr (sizeof(T) == 8 || J >= 7) {
 #pragma unroll 2
             for (int a = 0; a < JJ; ++a) {
                 if (a >= Jn) break;
@@ -614,12 +630,8 @@ void grid_tt(const Plan& P, const cpx<T>* y, const cpx<T>* gin, const int32_t* p
     const T* fr = (const T*)P.frac;
     const T* kbc = (const T*)P.kbpoly;
     const T* wt = (const T*)P.wtab;
-    switch (P.J) {
-        case 4: hipLaunchKernelGGL((k_grid<T, 4, TT, NT, C, GTG>), g, b, 0, s, y, gin, perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, 4); break;
-        case 6: hipLaunchKernelGGL((k_grid<T, 6, TT, NT, C, GTG>), g, b, 0, s, y, gin, perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, 6); break;
-        case 8: hipLaunchKernelGGL((k_grid<T, 8, TT, NT, C, GTG>), g, b, 0, s, y, gin, perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, 8); break;
-        default: hipLaunchKernelGGL((k_grid<T, 0, TT, NT, 1, GTG>), g, b, 0, s, y, gin, perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, P.J); break;
-    }
+    PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_grid<T, J_, TT, NT, (J_ > 0 ? C : 1), GTG>), g, b, 0, s, y, gin, perm,
+                                              P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, P.J));
     if (P.nmerge > 0)
         hipLaunchKernelGGL((k_grid_merge<T, TT>), dim3(P.nmerge), dim3(256), 0, s, P.gmerge, scr, P.gexp, grid, P.K, P.nT);
 }
@@ -637,12 +649,8 @@ void degrid_tiles_tt(const Plan& P, const cpx<T>* grid, cpx<T>* y, const int32_t
     const T* fr = (const T*)P.frac;
     const T* kbc = (const T*)P.kbpoly;
     const T* wt = (const T*)P.wtab;
-    switch (P.J) {
-        case 4: hipLaunchKernelGGL((k_degrid_tiles<T, 4, TT, 256>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, wt, work, P.K, nT, (T)scale, 4); break;
-        case 6: hipLaunchKernelGGL((k_degrid_tiles<T, 6, TT, 256>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, wt, work, P.K, nT, (T)scale, 6); break;
-        case 8: hipLaunchKernelGGL((k_degrid_tiles<T, 8, TT, 256>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, wt, work, P.K, nT, (T)scale, 8); break;
-        default: hipLaunchKernelGGL((k_degrid_tiles<T, 0, TT, 256>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, wt, work, P.K, nT, (T)scale, P.J); break;
-    }
+    PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_degrid_tiles<T, J_, TT, 256>), g, b, 0, s, grid, y, perm, P.base, fr,
+                                              kbc, wt, work, P.K, nT, (T)scale, P.J));
 }
 
 template <typename T>
@@ -661,12 +669,8 @@ void launch_degrid(const Plan& P, const cpx<T>* grid, cpx<T>* y, const int32_t* 
     const dim3 g(ch ? P.ndchunk : (M + 255) / 256), b(256);
     const T* fr = (const T*)P.frac;
     const T* kbc = (const T*)P.kbpoly;
-    switch (P.J) {
-        case 4: hipLaunchKernelGGL((k_degrid<T, 4>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, (const T*)P.wtab, M, P.K, (T)scale, 4, ch); break;
-        case 6: hipLaunchKernelGGL((k_degrid<T, 6>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, (const T*)P.wtab, M, P.K, (T)scale, 6, ch); break;
-        case 8: hipLaunchKernelGGL((k_degrid<T, 8>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, (const T*)P.wtab, M, P.K, (T)scale, 8, ch); break;
-        default: hipLaunchKernelGGL((k_degrid<T, 0>), g, b, 0, s, grid, y, perm, P.base, fr, kbc, (const T*)P.wtab, M, P.K, (T)scale, P.J, ch); break;
-    }
+    PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_degrid<T, J_>), g, b, 0, s, grid, y, perm, P.base, fr, kbc,
+                                              (const T*)P.wtab, M, P.K, (T)scale, P.J, ch));
 }
 
 template <typename T>

@@ -1,0 +1,28 @@
+"""Phi, Phi^dagger and Phi^dagger Phi for every kernel width with kernels of its own and the first
+runtime width, on both sides of the changes of kernel (512, where G^T G is one launch, and 1024),
+against the oracle.  Tolerances as for the other operator tests: a value sums J^2 products per
+visibility or cell, so rounding stays within 1e-12 (FP64) and 1e-5 (FP32) relative."""
+import numpy as np
+import pytest
+
+from gpu_cases import rand_complex, rel_l2, to_np, uv_case
+from oracle.nufft import Nufft
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,M,prec", [(32, 301, "fp64"), (64, 5003, "fp32"), (512, 20011, "fp32"),
+                                      (1024, 30011, "fp32"), (1024, 3001, "fp64")])
+@pytest.mark.parametrize("J", [2, 3, 5, 7, 9])
+def test_kernel_widths(n, M, prec, J):
+    from paper_1406_0359_amd import purify
+    uv = uv_case(M, n, 7 * J + n, 0.2)
+    op = Nufft(n, uv, J)
+    plan = purify.Plan(n, uv, J=J, levels=2, precision=prec)
+    x, y = rand_complex((n, n), J), rand_complex(M, J + 1)
+    if prec == "fp32":
+        x, y = x.astype(np.complex64), y.astype(np.complex64)
+    tol = 1e-12 if prec == "fp64" else 1e-5
+    assert rel_l2(to_np(plan.phi(plan.as_vec(x))), op.phi(x)) <= tol
+    assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= tol
+    assert rel_l2(to_np(plan.normal(plan.as_vec(x))), op.normal(x)) <= tol
