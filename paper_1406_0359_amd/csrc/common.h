@@ -130,6 +130,7 @@ struct Plan {
     int32_t* base = nullptr;     // M: packed first taps (k0_1 | k0_2 << 16), sorted order
     void* frac = nullptr;        // 2M reals: fractional offsets, sorted order
     int32_t* perm = nullptr;     // M: sorted position -> caller index
+    int32_t* inv = nullptr;      // M: caller index -> sorted position
     int32_t* tileoff = nullptr;  // 4 nT^2 + 1 class offsets
     int32_t* tilecover = nullptr;  // nT^2: max number of visibilities covering one cell of the tile
     int32_t* gwork = nullptr;    // gridding work-unit records, GRID_REC ints each
@@ -292,6 +293,11 @@ template <typename T> void launch_prox_ball(cpx<T>* v3, cpx<T>* z3, const cpx<T>
                                             double* hist, int hist_cap, int64_t n, bool diff, hipStream_t s);
 template <typename T> void launch_permute_scale(const cpx<T>* y_user, const int32_t* perm, double scale,
                                                 cpx<T>* y_sorted, int64_t n, hipStream_t s);
+// ys[inv[m]] = y_user[m]: caller order to sorted order
+template <typename T> void launch_sort_values(const cpx<T>* y_user, const int32_t* inv, cpx<T>* ys, int64_t n,
+                                              hipStream_t s);
+// inv[perm[p]] = p
+void launch_invert_perm(const int32_t* perm, int32_t* inv, int64_t n, hipStream_t s);
 template <typename T> void launch_scale_by_slot(cpx<T>* dst, const cpx<T>* src, const double* sc,
                                                 int slot, int64_t n, hipStream_t s);
 // Stored normal operator: v_m = exp(i omega_m . s) (sorted order); zero row / column 0 of an

@@ -675,6 +675,15 @@ void launch_degrid(const Plan& P, const cpx<T>* grid, cpx<T>* y, const int32_t* 
 
 template <typename T>
 void launch_grid(const Plan& P, const cpx<T>* y, const int32_t* perm, cpx<T>* grid, hipStream_t s) {
+    // Values in caller order are first put in sorted order where they outgrow the caches: a
+    // visibility's value is read once or twice for every tile that it reaches, and random 8- or
+    // 16-byte reads then fetch a line each (16.8 MB, 1024^2 FP32 with 2 M visibilities:
+    // Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between)
+    if (perm && (size_t)P.M * sizeof(cpx<T>) >= (size_t)12 << 20) {
+        launch_sort_values<T>(y, P.inv, (cpx<T>*)P.vis, P.M, s);
+        y = (const cpx<T>*)P.vis;
+        perm = nullptr;
+    }
     // FP32 32 x 32 tiles: 128 threads a unit (more units a CU; most units hold far fewer
     // visibilities than threads: 4096^2 G^T 503 -> 469 us, 1024^2 68.6 -> 64.0 us against 256)
     if (P.TT == 16) grid_tt<T, 16, 256, false>(P, y, nullptr, perm, grid, s);
@@ -683,11 +692,12 @@ void launch_grid(const Plan& P, const cpx<T>* y, const int32_t* perm, cpx<T>* gr
 
 template <typename T>
 void launch_gtg(const Plan& P, const cpx<T>* gin, cpx<T>* gout, hipStream_t s) {
-    if (sizeof(T) == 4 && P.K >= 2048) {
-        // FP32 grids from 2048 x 2048: G into the plan's visibility buffer, then G^T from it
-        // (the 64 x 64 degridding windows carry less halo than the fused launch's, and the
-        // one-item gridding batches in 128-thread units keep more units on a CU: 1024^2
-        // 97.8 -> 90.1 us, 4096^2 897 -> 737 us)
+    if (sizeof(T) == 4 && P.K >= 1024) {
+        // FP32 grids from 1024 x 1024: G into the plan's visibility buffer, then G^T from it
+        // (the degridding windows carry less halo than the fused launch's, and the one-item
+        // gridding batches keep more units on a CU: 1024^2 97.8 -> 90.1 us, 4096^2 897 -> 737
+        // us; Phi^dagger Phi at 512^2 with 7 taps 55.3 -> 51.8 us, with 8 82.8 -> 74.7, with 4
+        // to 6 the same)
         launch_degrid<T>(P, gin, (cpx<T>*)P.vis, nullptr, 1.0, s);
         launch_grid<T>(P, (const cpx<T>*)P.vis, nullptr, gout, s);
         return;

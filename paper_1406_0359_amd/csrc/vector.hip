@@ -322,6 +322,19 @@ k_permute_scale(const cpx<T>* __restrict__ yu, const int32_t* __restrict__ perm,
 
 template <typename T>
 __global__ void __launch_bounds__(VT)
+k_sort_values(const cpx<T>* __restrict__ yu, const int32_t* __restrict__ inv, cpx<T>* __restrict__ ys, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * VT + threadIdx.x;
+    if (i < n) ys[inv[i]] = yu[i];
+}
+
+__global__ void __launch_bounds__(VT)
+k_invert_perm(const int32_t* __restrict__ perm, int32_t* __restrict__ inv, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * VT + threadIdx.x;
+    if (i < n) inv[perm[i]] = (int32_t)i;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(VT)
 k_scale_by_slot(cpx<T>* __restrict__ dst, const cpx<T>* __restrict__ src, const double* __restrict__ sc,
                 int slot, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * VT + threadIdx.x;
@@ -547,6 +560,13 @@ void launch_permute_scale(const cpx<T>* y_user, const int32_t* perm, double scal
                        y_sorted, n);
 }
 template <typename T>
+void launch_sort_values(const cpx<T>* y_user, const int32_t* inv, cpx<T>* ys, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_sort_values<T>, dim3(ew_blocks(n)), dim3(VT), 0, s, y_user, inv, ys, n);
+}
+void launch_invert_perm(const int32_t* perm, int32_t* inv, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_invert_perm, dim3(ew_blocks(n)), dim3(VT), 0, s, perm, inv, n);
+}
+template <typename T>
 void launch_scale_by_slot(cpx<T>* dst, const cpx<T>* src, const double* sc, int slot, int64_t n,
                           hipStream_t s) {
     hipLaunchKernelGGL(k_scale_by_slot<T>, dim3(ew_blocks(n)), dim3(VT), 0, s, dst, src, sc, slot, n);
@@ -615,6 +635,7 @@ int launch_diff2_part(const cpx<T>* a, const cpx<T>* b, int64_t n, double* part_
                                       double, double*, double*, int, int64_t, bool, hipStream_t);       \
     template void launch_permute_scale<T>(const cpx<T>*, const int32_t*, double, cpx<T>*, int64_t,       \
                                           hipStream_t);                                                  \
+    template void launch_sort_values<T>(const cpx<T>*, const int32_t*, cpx<T>*, int64_t, hipStream_t);      \
     template void launch_scale_by_slot<T>(cpx<T>*, const cpx<T>*, const double*, int, int64_t, hipStream_t); \
     template void launch_ball_part_blk<T>(const cpx<T>*, const cpx<T>*, const cpx<T>*, const int32_t*,      \
                                           const int32_t*, int, double*, double*, hipStream_t);            \

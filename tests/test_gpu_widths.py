@@ -26,3 +26,16 @@ def test_kernel_widths(n, M, prec, J):
     assert rel_l2(to_np(plan.phi(plan.as_vec(x))), op.phi(x)) <= tol
     assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= tol
     assert rel_l2(to_np(plan.normal(plan.as_vec(x))), op.normal(x)) <= tol
+
+@pytest.mark.parametrize("n,M,prec", [(256, 1572864, "fp32"), (256, 1572863, "fp32"), (256, 786433, "fp64")])
+def test_adjoint_sorts_many_values(n, M, prec):
+    """Visibility vectors at and below 12 MiB (above it they are sorted before gridding)."""
+    from paper_1406_0359_amd import purify
+    uv = uv_case(M, n, M, 0.5)
+    op = Nufft(n, uv, 2)
+    plan = purify.Plan(n, uv, J=2, levels=2, precision=prec)
+    y = rand_complex(M, 3)
+    if prec == "fp32":
+        y = y.astype(np.complex64)
+    tol = 1e-12 if prec == "fp64" else 1e-5
+    assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= tol
