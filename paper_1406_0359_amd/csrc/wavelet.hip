@@ -49,6 +49,7 @@ struct Geo {
     static constexpr int LW = W1 > 32 ? 64 : 32;    // lanes that load one window row
     static constexpr int LR = NT / LW;              // rows loaded at a time
     static constexpr int RB = (W0 + LR - 1) / LR;   // loads a thread
+    static constexpr int RH = (C0 + LR - 1) / LR;   // synthesis: loads of the low, of the high rows
     // LDS strides.  Analysis windows keep pad elements after every 8 (a thread's P1 = 4
     // positions start 8 apart); synthesis windows hold the low and the high half of a row C1
     // apart, at an odd stride.
@@ -177,7 +178,7 @@ k_wav_fwd(const cpx<T>* __restrict__ src, size_t src_bstride, cpx<T>* __restrict
     {   // lane = column, all of a thread's rows in flight before any is stored
         const cpx<T>* s = src + (ALL || dirac ? 0 : (size_t)z0 * src_bstride);
         const int b = threadIdx.x % G::LW, a0 = threadIdx.x / G::LW;
-        const size_t co = (size_t)((c0 + b) & (Ls - 1));
+        const uint32_t co = (c0 + b) & (Ls - 1), lgs = __builtin_ctz(Ls);   // sides are powers of two
         T xs = 0;
         if constexpr (XHAT) xs = cg_alpha<T>(xa.rho_part, xa.rho_count, xa.pq_part, xa.pq_count);
         (void)xs;
@@ -188,7 +189,7 @@ k_wav_fwd(const cpx<T>* __restrict__ src, size_t src_bstride, cpx<T>* __restrict
                 // beyond the window: its last row again (a condition here would make the
                 // compiler wait for each load in a block of its own)
                 const int a = min(a0 + k * G::LR, R0 - 1);
-                const size_t o = (size_t)((r0 + a) & (Ls - 1)) * Ls + co;
+                const uint32_t o = ((uint32_t)((r0 + a) & (Ls - 1)) << lgs) + co;
                 v[k] = s[o];
                 if constexpr (XHAT) pv[k] = xa.p[o];
             }
@@ -284,10 +285,13 @@ k_wav_fwd(const cpx<T>* __restrict__ src, size_t src_bstride, cpx<T>* __restrict
 // axis 0.
 template <typename T, typename G>
 struct SynthWin {
-    T x[G::RB], y[G::RB];
+    T x[2 * G::RH], y[2 * G::RH];
 };
 
-// a thread's window elements (lane = window column) into registers
+// A thread's window elements (lane = window column) into registers: the low rows (the LL block
+// or the axis-1 detail), then the high rows (the two other details), positions past the filter's
+// own clamped to the last one as in k_wav_fwd.  Sides are powers of two, so a row's offset is a
+// shift (64-bit products took as many cycles here as a filter step).
 template <typename T, typename G>
 __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __restrict__ ab,
                                            const cpx<T>* __restrict__ lls, int lld, int n, int half, int m0, int m1,
@@ -297,18 +301,18 @@ __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __re
     const int b = tid % G::LW, a0 = tid / G::LW;
     const bool h1 = b >= C1;
     const int i1 = (s1 + (h1 ? b - C1 : b)) & (half - 1);
-    // low rows: the LL block or the axis-1 detail; high rows: the two other details
     const cpx<T>* lowp = h1 ? ab + half + i1 : lls + i1;
-    const int lowld = h1 ? n : lld;
+    const int lowsh = h1 ? __builtin_ctz(n) : __builtin_ctz(lld);
     const cpx<T>* highp = ab + (size_t)half * n + (h1 ? half + i1 : i1);
+    const int highsh = __builtin_ctz(n);
 #pragma unroll
-    for (int k = 0; k < G::RB; ++k) {
-        const int u = min(a0 + k * G::LR, 2 * C0 - 1);   // as in k_wav_fwd
-        const cpx<T>* q = u < C0 ? lowp + (size_t)((s0 + u) & (half - 1)) * lowld
-                                 : highp + (size_t)((s0 + u - C0) & (half - 1)) * n;
-        const cpx<T> c = *q;
-        w.x[k] = c.x;
-        w.y[k] = c.y;
+    for (int k = 0; k < G::RH; ++k) {
+        const uint32_t r = (s0 + min(a0 + k * G::LR, C0 - 1)) & (half - 1);
+        const cpx<T> l = lowp[r << lowsh], h = highp[r << highsh];
+        w.x[k] = l.x;
+        w.y[k] = l.y;
+        w.x[G::RH + k] = h.x;
+        w.y[G::RH + k] = h.y;
     }
 }
 
@@ -319,7 +323,11 @@ __device__ __forceinline__ void synth_store(const SynthWin<T, G>& w, int F, cpx<
     const int c = b >= C1 ? G::C1 + b - C1 : b;
     if (b >= 2 * C1) return;
 #pragma unroll
-    for (int k = 0; k < G::RB; ++k) in[min(a0 + k * G::LR, 2 * C0 - 1) * G::WS + c] = mk<T>(w.x[k], w.y[k]);
+    for (int k = 0; k < G::RH; ++k) {
+        cpx<T>* row = in + min(a0 + k * G::LR, C0 - 1) * G::WS + c;
+        row[0] = mk<T>(w.x[k], w.y[k]);
+        row[C0 * G::WS] = mk<T>(w.x[G::RH + k], w.y[G::RH + k]);
+    }
 }
 
 // undo axis 1: a thread per P1 sample pairs of a window row.  INPLACE: `mid` reuses `in`'s LDS
