@@ -276,8 +276,13 @@ __device__ __forceinline__ void lds_add(typename FixedAcc<T>::I* p, typename Fix
 // in the high half, so one 64-bit LDS atomic adds both.  Addition mod 2^64 gives
 // word = R 2^32 + I exactly; as |I| < 2^31 (the scale bound above), the low half read as
 // int32 is I, and (word - I) / 2^32 read as int32 is R.
-__device__ __forceinline__ unsigned long long pack_pair(int re, int im) {
-    return ((unsigned long long)(unsigned)re << 32) + (unsigned long long)(long long)im;
+// The word of round(w vx), round(w vy): the rounding sums' bit patterns are C + R and C + I, C =
+// 0x4B400000, both positive, so the pair taken as one 64-bit number is R 2^32 + I + C 2^32 + C,
+// and one 64-bit subtraction leaves the word (instead of two subtractions, a sign and a carry).
+__device__ __forceinline__ unsigned long long packed_product(float w, float vx, float vy) {
+    const unsigned long long re = (unsigned)__float_as_int(fmaf(w, vx, 12582912.0f));
+    const unsigned long long im = (unsigned)__float_as_int(fmaf(w, vy, 12582912.0f));
+    return ((re << 32) | im) - 0x4B4000004B400000ull;
 }
 __device__ __forceinline__ void unpack_pair(unsigned long long w, int& re, int& im) {
     im = (int)(unsigned)w;
@@ -504,9 +509,7 @@ k_grid(const cpx<T>* __restrict__ y, const cpx<T>* __restrict__ gin, const int32
                 for (int bb = 0; bb < JJ; ++bb) {
                     if (bb >= Jn) break;
                     if constexpr (PACK) {
-                        __hip_atomic_fetch_add(accp + (ap - acc) + a * WA + bb,
-                                               pack_pair((int)Acc::conv_mul(wb[c][bb], vx),
-                                                         (int)Acc::conv_mul(wb[c][bb], vy)),
+                        __hip_atomic_fetch_add(accp + (ap - acc) + a * WA + bb, packed_product(wb[c][bb], vx, vy),
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     } else {
                         lds_add<T>(ap + a * WA + bb, Acc::conv_mul(wb[c][bb], vx));
