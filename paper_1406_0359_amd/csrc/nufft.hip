@@ -13,6 +13,8 @@
 // footprint spills across the tile edge -- then writes the tile once.  No global atomics,
 // no halo buffers.  The plan sorts each tile's visibilities by spill class
 // [none | +k1 | +k1 and +k2 | +k2] so every neighbour's spill set is one contiguous range.
+#include <type_traits>
+
 #include "common.h"
 
 namespace purify {
@@ -564,6 +566,157 @@ k_grid(const cpx<T>* __restrict__ y, const cpx<T>* __restrict__ gin, const int32
 
 #undef PURIFY_STAGE_WINDOW
 
+// G^T in FP32 with four lanes a visibility, for widths with three or four tap pairs: k_grid's unit, accumulator and arithmetic (the same sums, bit for bit), but lane q of a quad
+// evaluates taps q and J - 1 - q of both axes -- one even/odd pair each -- and adds those two
+// columns of the footprint, row by row, with the rows' weights times the value broadcast from the
+// quad's lanes.  k_grid is bound by its LDS atomics: with a few visibilities a thread many lanes
+// have none in a round, and 64 lanes' single cells meet in the banks (4096^2: LDS busy 82% of the
+// time, 56% of that with conflicts); here a unit's rounds are full but for the last, and a quad's
+// cells are four neighbours.  256 threads a unit (128, 512: slower).  4096^2, J = 8: G^T 505 -> 430
+// us (Phi^dagger Phi 1710 -> 1640), 512^2, J = 7 49.4 -> 46.5, 1024^2, J = 6 (three lanes in four)
+// Phi^dagger 115 -> 113.
+typedef unsigned long long u64;
+
+// lane n of each quad to the quad
+template <int N>
+__device__ __forceinline__ float quad_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), N * 0x55, 0xF, 0xF, true));
+}
+
+template <int J, int TT, int NT>
+__global__ void __launch_bounds__(NT)
+k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, const int32_t* __restrict__ base,
+            const float* __restrict__ frac, const float* __restrict__ kbc, const int32_t* __restrict__ work,
+            int* __restrict__ partial, int32_t* __restrict__ pexp, cpx<float>* __restrict__ grid, int K, int nT) {
+    using Acc = FixedAcc<float>;
+    constexpr int NC = KBDeg<float>::value + 1, NP = (J + 1) / 2;
+    static_assert(NP == 3 || NP == 4, "a pair a lane");
+    constexpr int JM = J - 1, WA = TT + 2 * JM;   // margin and side of the padded accumulator
+    constexpr int NG = NT / 4;
+    __shared__ u64 acc[WA * WA];
+    __shared__ float red[NT / 64];
+    const int32_t* w = work + GRID_REC * blockIdx.x;
+    const int tile = w[0], slot = w[1], cover = w[2], total = w[3];
+    if (tile < 0) return;   // padding unit of the strip-ordered work list
+    const int t1o = (tile % nT) * TT, t2o = (tile / nT) * TT, mask = K - 1;
+    if (total == 0 && slot < 0) {   // no visibility reaches the tile
+        for (int i = threadIdx.x; i < TT * TT; i += NT)
+            grid[(size_t)(t1o + i / TT) * K + t2o + i % TT] = mk<float>(0, 0);
+        return;
+    }
+    // item j of the five ranges laid end to end
+    const int e1 = w[5] - w[4], e2 = e1 + w[7] - w[6], e3 = e2 + w[9] - w[8], e4 = e3 + w[11] - w[10];
+    const int d0 = w[4], d1 = w[6] - e1 - d0, d2 = w[8] - e2 - (w[6] - e1), d3 = w[10] - e3 - (w[8] - e2),
+              d4 = w[12] - e4 - (w[10] - e3);
+    auto item = [=](int j) {
+        return j + d0 + (j >= e1 ? d1 : 0) + (j >= e2 ? d2 : 0) + (j >= e3 ? d3 : 0) + (j >= e4 ? d4 : 0);
+    };
+    auto value = [&](int idx) { return y[perm ? perm[idx] : idx]; };
+    const cpx<float>* fr = reinterpret_cast<const cpx<float>*>(frac);
+    // each quad takes a contiguous chunk (the quads of a wave then add to different cells)
+    const int q = threadIdx.x & 3, ch = (total + NG - 1) / NG;
+    const int j0 = (int)(threadIdx.x >> 2) * ch, j1 = min(total, j0 + ch);
+    int idx = item(min(j0, total - 1)), bk = base[idx];
+    cpx<float> f = fr[idx], v = value(idx);
+    float c[NC];
+#pragma unroll
+    for (int d = 0; d < NC; ++d) c[d] = kbc[min(q, NP - 1) * NC + d];
+    for (int i = threadIdx.x; i < WA * WA; i += NT) acc[i] = 0;
+    // largest component, and the quantum, as in k_grid
+    float ymf = 0.0f;
+    for (int j = threadIdx.x; j < total; j += NT) {
+        const cpx<float> t = value(item(j));
+        ymf = fmaxf(ymf, fmaxf(fabsf(t.x), fabsf(t.y)));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ymf = fmaxf(ymf, __shfl_xor(ymf, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ymf;
+    __syncthreads();
+    double ym = 0.0;
+#pragma unroll
+    for (int wv = 0; wv < NT / 64; ++wv) ym = fmax(ym, (double)red[wv]);
+    const double bound = 2.0 * (double)cover * ym;
+    const bool any = bound > 0.0;
+    const int e = any ? max(ilogb(bound) + 1 - Acc::BITS, ilogb(2.0 * ym) + 1 - Acc::CBITS) : 0;
+    const float inv_q = (float)ldexp(1.0, -e);
+    if (any) {
+        for (int j = j0; j < j1; ++j) {
+            const cpx<float> fc = f, vc = v;
+            const int r0 = ((bk & 0xFFFF) - t1o + JM) & mask, c0 = (((bk >> 16) & 0xFFFF) - t2o + JM) & mask;
+            // the next item's loads are in flight meanwhile (past the chunk: its last item again)
+            idx = item(min(j + 1, j1 - 1));
+            bk = base[idx];
+            f = fr[idx];
+            v = value(idx);
+            // taps q (l) and J - 1 - q (h) of the two axes, as kb_weights
+            auto pair = [&](float fx, float& l, float& h) {
+                const float x = fx - 0.5f, x2 = x * x;
+                float ev = c[NC - 2], od = c[NC - 1];
+#pragma unroll
+                for (int d = NC - 4; d >= 0; d -= 2) {
+                    ev = fmaf(ev, x2, c[d]);
+                    od = fmaf(od, x2, c[d + 1]);
+                }
+                l = fmaf(x, od, ev);
+                h = fmaf(-x, od, ev);
+            };
+            float al, ah, bl, bh;
+            pair(fc.x, al, ah);
+            pair(fc.y, bl, bh);
+            if (2 * q == J - 1) {   // odd widths: the middle tap once
+                al = ah;
+                bl = bh;
+                bh = 0.0f;
+            }
+            const float sl = al * inv_q, sh = ah * inv_q;
+            const float lx = sl * vc.x, ly = sl * vc.y, hx = sh * vc.x, hy = sh * vc.y;
+            if (q < NP) {
+                u64* pl = acc + r0 * WA + c0 + q;
+                u64* ph = acc + r0 * WA + c0 + J - 1 - q;
+                auto row = [&](auto aa) {
+                    constexpr int a = decltype(aa)::value;
+                    if constexpr (a < J) {
+                        constexpr int src = a < NP ? a : J - 1 - a;
+                        const float rx = quad_bcast<src>(a < NP ? lx : hx), ry = quad_bcast<src>(a < NP ? ly : hy);
+                        __hip_atomic_fetch_add(pl + a * WA, packed_product(bl, rx, ry), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(ph + a * WA, packed_product(bh, rx, ry), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                };
+                row(std::integral_constant<int, 0>{});
+                row(std::integral_constant<int, 1>{});
+                row(std::integral_constant<int, 2>{});
+                row(std::integral_constant<int, 3>{});
+                row(std::integral_constant<int, 4>{});
+                row(std::integral_constant<int, 5>{});
+                row(std::integral_constant<int, 6>{});
+                row(std::integral_constant<int, 7>{});
+            }
+        }
+    }
+    __syncthreads();
+    const float qu = (float)ldexp(1.0, e);
+    const bool stream = K >= 8192;   // as in k_grid
+    int* pt = partial + (size_t)max(slot, 0) * 2 * TT * TT;
+    for (int i = threadIdx.x; i < TT * TT; i += NT) {
+        const int r = i / TT, cc = i % TT;
+        int re, im;
+        unpack_pair(acc[(r + JM) * WA + cc + JM], re, im);
+        cpx<float>* o = grid + (size_t)(t1o + r) * K + t2o + cc;
+        if (slot >= 0) {
+            pt[2 * i] = re;
+            pt[2 * i + 1] = im;
+        } else if (stream) {
+            __builtin_nontemporal_store(qu * (float)re, &o->x);
+            __builtin_nontemporal_store(qu * (float)im, &o->y);
+        } else {
+            *o = mk<float>(qu * (float)re, qu * (float)im);
+        }
+    }
+    if (slot >= 0 && threadIdx.x == 0) pexp[slot] = e;
+}
+
 // Sum of the partial tiles of each split tile (one workgroup per split tile), in part order
 // and in double, then written to the grid.
 template <typename T, int TT>
@@ -633,8 +786,20 @@ void grid_tt(const Plan& P, const cpx<T>* y, const cpx<T>* gin, const int32_t* p
     const T* fr = (const T*)P.frac;
     const T* kbc = (const T*)P.kbpoly;
     const T* wt = (const T*)P.wtab;
-    PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_grid<T, J_, TT, NT, (J_ > 0 ? C : 1), GTG>), g, b, 0, s, y, gin, perm,
-                                              P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, P.J));
+    bool quad = false;
+    if constexpr (sizeof(T) == 4 && !GTG) {
+        // J = 6 to 8; with five taps the pairs fill three of a quad's lanes, the last for one
+        // column (2048^2, 2 10^6 visibilities: 371 -> 375 us)
+        quad = P.J >= 6 && P.J <= 8;
+        if (quad)
+            PURIFY_J_DISPATCH(P.J, if constexpr (J_ >= 6) hipLaunchKernelGGL(
+                                       (k_grid_quad<J_, TT, 256>), g, dim3(256), 0, s, y, perm, P.base, fr, kbc, P.gwork,
+                                       scr, P.gexp, grid, P.K, P.nT));
+    }
+    if (!quad)
+        PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_grid<T, J_, TT, NT, (J_ > 0 ? C : 1), GTG>), g, b, 0, s, y, gin,
+                                                  perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT,
+                                                  P.J));
     if (P.nmerge > 0)
         hipLaunchKernelGGL((k_grid_merge<T, TT>), dim3(P.nmerge), dim3(256), 0, s, P.gmerge, scr, P.gexp, grid, P.K, P.nT);
 }
@@ -687,7 +852,7 @@ void launch_grid(const Plan& P, const cpx<T>* y, const int32_t* perm, cpx<T>* gr
         y = (const cpx<T>*)P.vis;
         perm = nullptr;
     }
-    // FP32 32 x 32 tiles: 128 threads a unit (more units a CU; most units hold far fewer
+    // FP32 32 x 32 tiles by k_grid: 128 threads a unit (more units a CU; most units hold far fewer
     // visibilities than threads: 4096^2 G^T 503 -> 469 us, 1024^2 68.6 -> 64.0 us against 256)
     if (P.TT == 16) grid_tt<T, 16, 256, false>(P, y, nullptr, perm, grid, s);
     else grid_tt<T, 32, sizeof(T) == 4 ? 128 : 256, false>(P, y, nullptr, perm, grid, s);
