@@ -290,15 +290,21 @@ struct SynthWin {
 
 // A thread's window elements (lane = window column) into registers: the low rows (the LL block
 // or the axis-1 detail), then the high rows (the two other details), positions past the filter's
-// own clamped to the last one as in k_wav_fwd.  Sides are powers of two, so a row's offset is a
+// own clamped to the last one as in k_wav_fwd.  SKIP leaves out loads wholly past it (only where
+// a barrier parts the loads from the stores, or the compiler joins the two blocks), and takes two
+// rows a wave where a row is at most 32 columns (Psi 1024^2 FP32 57.7 -> 56.3 us, 4096^2 629 -> 617,
+// 4096^2 with Db1 and Db2 alone 161 -> 150).  Sides are powers of two, so a row's offset is a
 // shift (64-bit products took as many cycles here as a filter step).
-template <typename T, typename G>
+template <typename T, typename G, bool SKIP>
 __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __restrict__ ab,
                                            const cpx<T>* __restrict__ lls, int lld, int n, int half, int m0, int m1,
                                            int F, int tid) {
     const int C0 = G::TP0 + F / 2 - 1, C1 = G::TP1 + F / 2 - 1;
     const int s0 = m0 / 2 - F / 2 + 1, s1 = m1 / 2 - F / 2 + 1;   // first window index
-    const int b = tid % G::LW, a0 = tid / G::LW;
+    // windows of at most half a wave's lanes: two rows a wave
+    const bool narrow = SKIP && G::LW == 64 && 2 * C1 <= 32;
+    const int b = narrow ? tid & 31 : tid % G::LW, a0 = narrow ? tid >> 5 : tid / G::LW;
+    const int LR = narrow ? 2 * G::LR : G::LR;
     const bool h1 = b >= C1;
     const int i1 = (s1 + (h1 ? b - C1 : b)) & (half - 1);
     const cpx<T>* lowp = h1 ? ab + half + i1 : lls + i1;
@@ -307,7 +313,8 @@ __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __re
     const int highsh = __builtin_ctz(n);
 #pragma unroll
     for (int k = 0; k < G::RH; ++k) {
-        const uint32_t r = (s0 + min(a0 + k * G::LR, C0 - 1)) & (half - 1);
+        if (SKIP && k * LR >= C0) break;
+        const uint32_t r = (s0 + min(a0 + k * LR, C0 - 1)) & (half - 1);
         const cpx<T> l = lowp[r << lowsh], h = highp[r << highsh];
         w.x[k] = l.x;
         w.y[k] = l.y;
@@ -316,15 +323,19 @@ __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __re
     }
 }
 
-template <typename T, typename G>
+template <typename T, typename G, bool SKIP>
 __device__ __forceinline__ void synth_store(const SynthWin<T, G>& w, int F, cpx<T>* in, int tid) {
     const int C0 = G::TP0 + F / 2 - 1, C1 = G::TP1 + F / 2 - 1;
-    const int b = tid % G::LW, a0 = tid / G::LW;
+    // windows of at most half a wave's lanes: two rows a wave
+    const bool narrow = SKIP && G::LW == 64 && 2 * C1 <= 32;
+    const int b = narrow ? tid & 31 : tid % G::LW, a0 = narrow ? tid >> 5 : tid / G::LW;
+    const int LR = narrow ? 2 * G::LR : G::LR;
     const int c = b >= C1 ? G::C1 + b - C1 : b;
     if (b >= 2 * C1) return;
 #pragma unroll
     for (int k = 0; k < G::RH; ++k) {
-        cpx<T>* row = in + min(a0 + k * G::LR, C0 - 1) * G::WS + c;
+        if (SKIP && k * LR >= C0) break;
+        cpx<T>* row = in + min(a0 + k * LR, C0 - 1) * G::WS + c;
         row[0] = mk<T>(w.x[k], w.y[k]);
         row[C0 * G::WS] = mk<T>(w.x[G::RH + k], w.y[G::RH + k]);
     }
@@ -405,9 +416,9 @@ k_wav_inv_level(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ lli
     const int tid = threadIdx.x;
     {
         SynthWin<T, G> w;
-        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
+        synth_load<T, G, false>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
                          m1, F, tid);
-        synth_store<T, G>(w, F, in, tid);
+        synth_store<T, G, false>(w, F, in, tid);
     }
     __syncthreads();
     synth_axis1<T, G, false>(F, h, in, mid, tid, true);
@@ -456,9 +467,9 @@ k_wav_inv_final(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ lli
     const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
     {
         SynthWin<T, G> w;
-        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
+        synth_load<T, G, false>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), ll_from_alpha ? n : half, n, half, m0,
                          m1, F, tid);
-        synth_store<T, G>(w, F, in, tid);
+        synth_store<T, G, false>(w, F, in, tid);
     }
     // the tile's Dirac samples are read before the barriers
     const int pix = threadIdx.x;
@@ -526,10 +537,10 @@ k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict_
     SynthWin<T, G> w;
     auto load = [&](int z) {
         const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
-        synth_load<T, G>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), lld, n, half, m0, m1, A.flen[z], tid);
+        synth_load<T, G, true>(w, ab, ll_from_alpha ? ab : llin + (size_t)z * (N / 4), lld, n, half, m0, m1, A.flen[z], tid);
     };
     load(0);
-    synth_store<T, G>(w, A.flen[0], in, tid);
+    synth_store<T, G, true>(w, A.flen[0], in, tid);
     __syncthreads();
     for (int z = 0; z < A.nwav; ++z) {
         const int F = A.flen[z];
@@ -549,7 +560,7 @@ k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict_
                 o[p] = o[p] + bo[p];
             }
         }
-        if (more) synth_store<T, G>(w, A.flen[z + 1], in, tid);
+        if (more) synth_store<T, G, true>(w, A.flen[z + 1], in, tid);
         __syncthreads();
     }
     if (!on) return;
