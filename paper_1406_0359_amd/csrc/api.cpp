@@ -613,6 +613,14 @@ void run_stage(const Plan& P, int stage, hipStream_t s) {
 
 bool f64(const Plan& P) { return P.precision == PURIFY_FP64; }
 
+// the sorted position of each visibility, on the device from the uploaded permutation
+purify_status build_inverse(const Plan& P, hipStream_t s) {
+    launch_invert_perm(P.perm, P.inv, P.M, s);
+    PURIFY_HIP(hipGetLastError());
+    PURIFY_HIP(hipStreamSynchronize(s));
+    return PURIFY_OK;
+}
+
 }  // namespace
 
 void set_error(const std::string& msg) { g_last_error = msg; }
@@ -693,7 +701,8 @@ purify_status purify_plan_create(const purify_plan_desc* desc, void* workspace, 
     P.ss = &h->own;
     P.ws = (char*)workspace;
     P.ws_bytes = bytes;
-    const purify_status st = build_plan(P, desc, (hipStream_t)stream);
+    purify_status st = build_plan(P, desc, (hipStream_t)stream);
+    if (st == PURIFY_OK && P.inv) st = build_inverse(P, (hipStream_t)stream);
     if (st != PURIFY_OK) {
         delete h;
         return st;

@@ -130,7 +130,7 @@ struct Plan {
     int32_t* base = nullptr;     // M: packed first taps (k0_1 | k0_2 << 16), sorted order
     void* frac = nullptr;        // 2M reals: fractional offsets, sorted order
     int32_t* perm = nullptr;     // M: sorted position -> caller index
-    int32_t* inv = nullptr;      // M: caller index -> sorted position
+    int32_t* inv = nullptr;      // M: caller index -> sorted position (null unless sorts_values)
     int32_t* tileoff = nullptr;  // 4 nT^2 + 1 class offsets
     int32_t* tilecover = nullptr;  // nT^2: max number of visibilities covering one cell of the tile
     int32_t* gwork = nullptr;    // gridding work-unit records, GRID_REC ints each
@@ -184,6 +184,12 @@ struct Plan {
     // streams and events the solver runs on (the plan's own, or a server slot's)
     SolverStreams* ss = nullptr;
 };
+
+// The adjoint puts values in caller order into sorted order first where they outgrow the caches:
+// a visibility's value is read once or twice for every tile that it reaches, and random 8- or
+// 16-byte reads then fetch a line each (16.8 MB, 1024^2 FP32 with 2 M visibilities:
+// Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between).
+inline bool sorts_values(const Plan& P) { return (size_t)P.M * P.elem >= (size_t)12 << 20; }
 
 // ---------------------------------------------------------------------------------------
 // Kernel launchers (defined in the .hip files, instantiated for float and double).

@@ -24,8 +24,8 @@ namespace {
 
 // CALL with J_ = P.J for the widths with kernels of their own (up to 8; unrolled taps and
 // margins of the width itself), J_ = 0 for wider ones, whose kernels loop over a runtime width
-// (512^2 FP32, J = 7, 180221 visibilities: G^T G 107 us by the runtime
-// kernel, 32 by its own).
+// (512^2 FP32, J = 7, 180221 visibilities: Phi^dagger Phi 131 us by the runtime kernels, 55 by
+// its own).
 #define PURIFY_J_DISPATCH(J_VAR, CALL)                  \
     switch (J_VAR) {                                    \
         case 2: { constexpr int J_ = 2; CALL; } break;  \
@@ -797,9 +797,9 @@ void grid_tt(const Plan& P, const cpx<T>* y, const cpx<T>* gin, const int32_t* p
                                        scr, P.gexp, grid, P.K, P.nT));
     }
     if (!quad)
-        PURIFY_J_DISPATCH(P.J, hipLaunchKernelGGL((k_grid<T, J_, TT, NT, (J_ > 0 ? C : 1), GTG>), g, b, 0, s, y, gin,
-                                                  perm, P.base, fr, kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT,
-                                                  P.J));
+        PURIFY_J_DISPATCH(P.J, if constexpr (sizeof(T) == 8 || GTG || J_ < 6) hipLaunchKernelGGL(
+                                   (k_grid<T, J_, TT, NT, (J_ > 0 ? C : 1), GTG>), g, b, 0, s, y, gin, perm, P.base, fr,
+                                   kbc, wt, P.gwork, scr, P.gexp, grid, P.K, P.nT, P.J));
     if (P.nmerge > 0)
         hipLaunchKernelGGL((k_grid_merge<T, TT>), dim3(P.nmerge), dim3(256), 0, s, P.gmerge, scr, P.gexp, grid, P.K, P.nT);
 }
@@ -843,17 +843,14 @@ void launch_degrid(const Plan& P, const cpx<T>* grid, cpx<T>* y, const int32_t* 
 
 template <typename T>
 void launch_grid(const Plan& P, const cpx<T>* y, const int32_t* perm, cpx<T>* grid, hipStream_t s) {
-    // Values in caller order are first put in sorted order where they outgrow the caches: a
-    // visibility's value is read once or twice for every tile that it reaches, and random 8- or
-    // 16-byte reads then fetch a line each (16.8 MB, 1024^2 FP32 with 2 M visibilities:
-    // Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between)
-    if (perm && (size_t)P.M * sizeof(cpx<T>) >= (size_t)12 << 20) {
+    if (perm && sorts_values(P)) {
         launch_sort_values<T>(y, P.inv, (cpx<T>*)P.vis, P.M, s);
         y = (const cpx<T>*)P.vis;
         perm = nullptr;
     }
     // FP32 32 x 32 tiles by k_grid: 128 threads a unit (more units a CU; most units hold far fewer
-    // visibilities than threads: 4096^2 G^T 503 -> 469 us, 1024^2 68.6 -> 64.0 us against 256)
+    // visibilities than threads: 4096^2 G^T 503 -> 469 us, 1024^2 68.6 -> 64.0 us against 256,
+    // with the 8 and 6 taps that k_grid_quad now takes)
     if (P.TT == 16) grid_tt<T, 16, 256, false>(P, y, nullptr, perm, grid, s);
     else grid_tt<T, 32, sizeof(T) == 4 ? 128 : 256, false>(P, y, nullptr, perm, grid, s);
 }
@@ -870,8 +867,10 @@ void launch_gtg(const Plan& P, const cpx<T>* gin, cpx<T>* gout, hipStream_t s) {
         launch_grid<T>(P, (const cpx<T>*)P.vis, nullptr, gout, s);
         return;
     }
-    if (P.TT == 16) grid_tt<T, 16, 256, true>(P, nullptr, gin, nullptr, gout, s);
-    else grid_tt<T, 32, 256, true>(P, nullptr, gin, nullptr, gout, s);
+    // 32 x 32 tiles (K > 1024): FP64 only
+    if constexpr (sizeof(T) == 8)
+        if (P.TT == 32) return grid_tt<T, 32, 256, true>(P, nullptr, gin, nullptr, gout, s);
+    grid_tt<T, 16, 256, true>(P, nullptr, gin, nullptr, gout, s);
 }
 
 template void launch_degrid<float>(const Plan&, const cpx<float>*, cpx<float>*, const int32_t*, double, hipStream_t);

@@ -272,7 +272,7 @@ size_t layout(Plan& P, const purify_plan_desc* d, char* ws) {
     P.base = (int32_t*)carve(M * 4);
     P.frac = carve(2 * M * es);
     P.perm = (int32_t*)carve(M * 4);
-    P.inv = (int32_t*)carve(M * 4);
+    P.inv = sorts_values(P) ? (int32_t*)carve(M * 4) : nullptr;
     P.tileoff = (int32_t*)carve(((size_t)4 * P.nT * P.nT + 1) * 4);
     P.tilecover = (int32_t*)carve((size_t)P.nT * P.nT * 4);
     // Gridding work units: a tile whose visibility list (own + spill-ins) exceeds
@@ -854,7 +854,6 @@ purify_status build_plan(Plan& P, const purify_plan_desc* d, hipStream_t s) {
     };
     PURIFY_HIP(up(P.base, sbase.data(), M * 4));
     PURIFY_HIP(up(P.perm, perm.data(), M * 4));
-    launch_invert_perm(P.perm, P.inv, M, s);
     PURIFY_HIP(up(P.tileoff, off.data(), off.size() * 4));
     PURIFY_HIP(up(P.tilecover, cover.data(), cover.size() * 4));
     PURIFY_HIP(up(P.gwork, work.data(), work.size() * sizeof(int32_t)));

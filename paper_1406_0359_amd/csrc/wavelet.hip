@@ -154,7 +154,7 @@ __device__ __forceinline__ void synthesise(const cpx<T>* lo, const cpx<T>* hi, c
 // Bound: large images by the write of the coefficients (4096^2, nine bases and five levels: 1.34
 // GB in and out, 275 us at the copy rate of 4.9 TB/s) beside about as much arithmetic; small ones
 // by the latency of a launch's window, taps and two steps.  With register-blocked steps of fixed
-// filter length 4096^2 FP32 takes 508 us (644 before), 1024^2 43 (63), 256^2 FP64 19 (32).
+// filter length 4096^2 FP32 takes 503 us (644 before), 1024^2 43 (63), 256^2 FP64 19 (32).
 template <typename T, typename G, bool ALL, bool XHAT>
 __global__ void __launch_bounds__(G::NT)
 k_wav_fwd(const cpx<T>* __restrict__ src, size_t src_bstride, cpx<T>* __restrict__ alpha,
@@ -512,7 +512,7 @@ k_wav_inv_final(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ lli
 // its second step, so the loads have both steps to arrive.  The sums over the bases stay in
 // registers.
 // Bound by the windows' loads (1.5 times the coefficients, the halos from L2): 1024^2 FP32 whole
-// synthesis 75 -> 58 us, 4096^2 789 -> 730 us, 1024^2 FP64 195 -> 91 us.
+// synthesis 75 -> 56 us, 4096^2 789 -> 617 us, 1024^2 FP64 195 -> 91 us.
 template <typename T, typename G>
 __global__ void __launch_bounds__(G::NT)
 k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
