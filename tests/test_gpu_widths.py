@@ -27,6 +27,7 @@ def test_kernel_widths(n, M, prec, J):
     assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= tol
     assert rel_l2(to_np(plan.normal(plan.as_vec(x))), op.normal(x)) <= tol
 
+
 @pytest.mark.parametrize("n,M,prec", [(256, 1572864, "fp32"), (256, 1572863, "fp32"), (256, 786433, "fp64")])
 def test_adjoint_sorts_many_values(n, M, prec):
     """Visibility vectors at and below 12 MiB (above it they are sorted before gridding)."""
@@ -39,3 +40,20 @@ def test_adjoint_sorts_many_values(n, M, prec):
         y = y.astype(np.complex64)
     tol = 1e-12 if prec == "fp64" else 1e-5
     assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= tol
+
+
+def test_fp32_lines_of_2048_and_4096():
+    """Lines of 2048 points (the shortest with the two short twiddle tables) as row, column and
+    stored-operator transforms of a 2048^2 image; the stored operator against the NUFFT normal
+    operator at that operator's own error (1e-4)."""
+    from paper_1406_0359_amd import purify
+    n, M, J = 2048, 40013, 8
+    uv = uv_case(M, n, 11, 0.2)
+    op = Nufft(n, uv, J)
+    plan = purify.Plan(n, uv, J=J, levels=2, precision="fp32")
+    x, y = rand_complex((n, n), 5).astype(np.complex64), rand_complex(M, 6).astype(np.complex64)
+    assert rel_l2(to_np(plan.phi(plan.as_vec(x))), op.phi(x)) <= 1e-5
+    assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= 1e-5
+    normal = op.normal(x)
+    assert rel_l2(to_np(plan.normal(plan.as_vec(x))), normal) <= 1e-5
+    assert rel_l2(to_np(plan.normal(plan.as_vec(x), toeplitz=True)), normal) <= 1e-4
