@@ -516,16 +516,16 @@ k_wav_inv_final(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ lli
 template <typename T, typename G>
 __global__ void __launch_bounds__(G::NT)
 k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
-                     cpx<T>* __restrict__ x, const T* __restrict__ filt, WavArgs A, T scale) {
+                     cpx<T>* __restrict__ x, const T* __restrict__ filt, WavArgs A, int raster, T scale) {
     __shared__ __attribute__((aligned(16))) cpx<T> in[G::W0 * G::WS];
     __shared__ __attribute__((aligned(16))) cpx<T> mid[2 * G::C0 * G::MS];
     const int n = A.n;
     const size_t N = (size_t)n * n;
     const int half = n >> 1;
     const int tiles1 = n / (2 * G::TP1);
-    // each XCD takes a contiguous range of tiles, so that the windows' halos meet in one L2
+    // unless raster, each XCD takes a contiguous range of tiles, so that the windows' halos meet in one L2
     // (1024^2 FP32 64 -> 58 us, FP64 98 -> 91 us; the analysis, which writes, lost 4% so)
-    const int bx = gridDim.x % 8 ? blockIdx.x : (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const int bx = raster || gridDim.x % 8 ? blockIdx.x : (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     const int m0 = 2 * G::TP0 * (bx / tiles1), m1 = 2 * G::TP1 * (bx % tiles1);
     const int tid = threadIdx.x;
     const int lld = ll_from_alpha ? n : half;
@@ -656,8 +656,15 @@ void inv_level(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T
 template <typename T, typename G>
 void inv_final_pipe(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T>* in, int from_alpha, cpx<T>* x,
                     T scale, hipStream_t s) {
+    // Filters of at most four taps have hardly a halo to share in an L2; once image and coefficients
+    // outgrow the 256 MB last-level cache their tiles go in raster order, all XCDs on one stretch
+    // of memory (4096^2 FP32, Db1 and Db2 150 -> 146 us, Db1 93 -> 87; 2048^2 37.9 -> 40.6 us, and with
+    // all nine bases 4096^2 617 -> 643, so neither of those)
+    int fmax = 0;
+    for (int z = 0; z < A.nwav; ++z) fmax = std::max(fmax, A.flen[z]);
+    const int raster = fmax <= 4 && (size_t)(A.nwav + 1) * P.N * sizeof(cpx<T>) >= (size_t)256 << 20;
     hipLaunchKernelGGL((k_wav_inv_final_pipe<T, G>), dim3(P.N / (4 * G::TP0 * G::TP1)), dim3(G::NT), 0, s, alpha, in,
-                       from_alpha, x, (const T*)P.filters, A, scale);
+                       from_alpha, x, (const T*)P.filters, A, raster, scale);
 }
 
 template <typename T>

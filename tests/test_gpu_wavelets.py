@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (16, 0x1FF, 4, "fp64"), (16, 1 << 8, 1, "fp32"), (32, 0x002, 5, "fp64"), (32, 0x1FE, 2, "fp32"),
     (64, 0x104, 6, "fp32"), (128, 0x1FF, 3, "fp32"), (256, 0x1FF, 1, "fp64"), (256, 0x003, 4, "fp64"),
     (512, 0x1FE, 5, "fp64"), (512, 0x041, 2, "fp32"), (1024, 0x00D, 3, "fp32"), (1024, 0x0F0, 2, "fp64"),
+    (4096, 0x003, 2, "fp32"),
 ])
 def test_dictionary_edges(n, mask, levels, prec):
     from paper_1406_0359_amd import purify
