@@ -531,9 +531,20 @@ k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict_
     const int lld = ll_from_alpha ? n : half;
     const int col = tid % (2 * G::TP1), g0 = tid / (2 * G::TP1);
     const bool on = g0 < G::TP0 / G::P0;
+    const size_t off = (size_t)(m0 + 2 * G::P0 * g0) * n + m1 + col;
+    // the sums start from the Dirac block, whose loads then run beside the first window's (loaded
+    // after the bases: 4096^2 FP32 Psi 619 -> 612 us, Dirac + Db8 157 -> 140, Dirac + Db1 106 -> 99,
+    // 1024^2 57 -> 56)
     cpx<T> e[G::P0], o[G::P0];
 #pragma unroll
-    for (int p = 0; p < G::P0; ++p) e[p] = o[p] = mk<T>(0, 0);
+    for (int p = 0; p < G::P0; ++p) {
+        e[p] = o[p] = mk<T>(0, 0);
+        if (A.dirac_block >= 0 && on) {
+            const cpx<T>* d = alpha + (size_t)A.dirac_block * N + off + (size_t)(2 * p) * n;
+            e[p] = d[0];
+            o[p] = d[n];
+        }
+    }
     SynthWin<T, G> w;
     auto load = [&](int z) {
         const cpx<T>* ab = alpha + (size_t)A.block[z] * N;
@@ -564,17 +575,11 @@ k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict_
         __syncthreads();
     }
     if (!on) return;
-    const size_t off = (size_t)(m0 + 2 * G::P0 * g0) * n + m1 + col;
 #pragma unroll
     for (int p = 0; p < G::P0; ++p) {
-        const size_t a = off + (size_t)(2 * p) * n, b = a + n;
-        if (A.dirac_block >= 0) {
-            const cpx<T>* d = alpha + (size_t)A.dirac_block * N;
-            e[p] = e[p] + d[a];
-            o[p] = o[p] + d[b];
-        }
+        const size_t a = off + (size_t)(2 * p) * n;
         x[a] = scale * e[p];
-        x[b] = scale * o[p];
+        x[a + n] = scale * o[p];
     }
 }
 
