@@ -185,11 +185,18 @@ struct Plan {
     SolverStreams* ss = nullptr;
 };
 
-// The adjoint puts values in caller order into sorted order first where they outgrow the caches:
-// a visibility's value is read once or twice for every tile that it reaches, and random 8- or
-// 16-byte reads then fetch a line each (16.8 MB, 1024^2 FP32 with 2 M visibilities:
+// FP32 gridding of values in caller order by k_grid_quad keeps a work unit's values in LDS (its
+// figures are there), up to 2048 values: with 16 KB more still five workgroups of 32 x 32 tiles a CU.
+inline bool stages_values(const Plan& P) {
+    return P.precision == PURIFY_FP32 && P.J >= 6 && P.J <= 8 && P.grid_unit <= 2048;
+}
+// Elsewhere the adjoint puts values in caller order into sorted order first where they outgrow the
+// caches: a visibility's value is read once or twice for every tile that it reaches, and random 8-
+// or 16-byte reads then fetch a line each (16.8 MB in FP32, 1024^2, before values were staged:
 // Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between).
-inline bool sorts_values(const Plan& P) { return (size_t)P.M * P.elem >= (size_t)12 << 20; }
+inline bool sorts_values(const Plan& P) {
+    return !stages_values(P) && (size_t)P.M * P.elem >= (size_t)12 << 20;
+}
 
 // ---------------------------------------------------------------------------------------
 // Kernel launchers (defined in the .hip files, instantiated for float and double).

@@ -575,6 +575,11 @@ k_grid(const cpx<T>* __restrict__ y, const cpx<T>* __restrict__ gin, const int32
 // cells are four neighbours.  256 threads a unit (128, 512: slower).  4096^2, J = 8: G^T 505 -> 430
 // us (Phi^dagger Phi 1710 -> 1640), 512^2, J = 7 49.4 -> 46.5, 1024^2, J = 6 (three lanes in four)
 // Phi^dagger 115 -> 113.
+// STAGE (values in caller order): the pass for the largest component keeps the unit's values in
+// LDS, four loads a thread in flight, so that each is read once, not twice, from its random place
+// and not in the chain of the additions: Phi^dagger 1024^2 FP32, J = 6, 2 M visibilities (sorted
+// by a pass of its own before) 114 -> 101 us, 1 M 76.9 -> 64.9, 2048^2 with 4 M 286 -> 267, 256^2 with
+// 60000 19.1 -> 16.8.  Values in sorted order gain nothing by it (4096^2 G^T G 1646 -> 1679 us).
 typedef unsigned long long u64;
 
 // lane n of each quad to the quad
@@ -583,7 +588,7 @@ __device__ __forceinline__ float quad_bcast(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), N * 0x55, 0xF, 0xF, true));
 }
 
-template <int J, int TT, int NT>
+template <int J, int TT, int NT, bool STAGE>
 __global__ void __launch_bounds__(NT)
 k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, const int32_t* __restrict__ base,
             const float* __restrict__ frac, const float* __restrict__ kbc, const int32_t* __restrict__ work,
@@ -594,6 +599,7 @@ k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, 
     constexpr int JM = J - 1, WA = TT + 2 * JM;   // margin and side of the padded accumulator
     constexpr int NG = NT / 4;
     __shared__ u64 acc[WA * WA];
+    extern __shared__ __attribute__((aligned(8))) cpx<float> vals[];   // STAGE: the unit's values
     __shared__ float red[NT / 64];
     const int32_t* w = work + GRID_REC * blockIdx.x;
     const int tile = w[0], slot = w[1], cover = w[2], total = w[3];
@@ -611,22 +617,51 @@ k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, 
     auto item = [=](int j) {
         return j + d0 + (j >= e1 ? d1 : 0) + (j >= e2 ? d2 : 0) + (j >= e3 ? d3 : 0) + (j >= e4 ? d4 : 0);
     };
-    auto value = [&](int idx) { return y[perm ? perm[idx] : idx]; };
+    // the value of item j, sorted position idx
+    auto value = [&](int j, int idx) {
+        if constexpr (STAGE) return vals[j];
+        else return y[perm ? perm[idx] : idx];
+    };
     const cpx<float>* fr = reinterpret_cast<const cpx<float>*>(frac);
     // each quad takes a contiguous chunk (the quads of a wave then add to different cells)
     const int q = threadIdx.x & 3, ch = (total + NG - 1) / NG;
     const int j0 = (int)(threadIdx.x >> 2) * ch, j1 = min(total, j0 + ch);
     int idx = item(min(j0, total - 1)), bk = base[idx];
-    cpx<float> f = fr[idx], v = value(idx);
+    cpx<float> f = fr[idx], v;
+    if constexpr (!STAGE) v = value(j0, idx);
     float c[NC];
 #pragma unroll
     for (int d = 0; d < NC; ++d) c[d] = kbc[min(q, NP - 1) * NC + d];
     for (int i = threadIdx.x; i < WA * WA; i += NT) acc[i] = 0;
     // largest component, and the quantum, as in k_grid
     float ymf = 0.0f;
-    for (int j = threadIdx.x; j < total; j += NT) {
-        const cpx<float> t = value(item(j));
-        ymf = fmaxf(ymf, fmaxf(fabsf(t.x), fabsf(t.y)));
+    if constexpr (STAGE) {
+        // four values a thread in flight (past the unit: its last item again)
+        for (int j = threadIdx.x; j < total; j += 4 * NT) {
+            int pi[4];
+            float tx[4], ty[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int idx = item(min(j + k * NT, total - 1));
+                pi[k] = perm ? perm[idx] : idx;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const cpx<float> t = y[pi[k]];
+                tx[k] = t.x;
+                ty[k] = t.y;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                vals[min(j + k * NT, total - 1)] = mk<float>(tx[k], ty[k]);
+                ymf = fmaxf(ymf, fmaxf(fabsf(tx[k]), fabsf(ty[k])));
+            }
+        }
+    } else {
+        for (int j = threadIdx.x; j < total; j += NT) {
+            const cpx<float> t = value(j, item(j));
+            ymf = fmaxf(ymf, fmaxf(fabsf(t.x), fabsf(t.y)));
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ymf = fmaxf(ymf, __shfl_xor(ymf, o));
@@ -640,14 +675,16 @@ k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, 
     const int e = any ? max(ilogb(bound) + 1 - Acc::BITS, ilogb(2.0 * ym) + 1 - Acc::CBITS) : 0;
     const float inv_q = (float)ldexp(1.0, -e);
     if (any) {
+        if constexpr (STAGE) v = vals[min(j0, total - 1)];
         for (int j = j0; j < j1; ++j) {
             const cpx<float> fc = f, vc = v;
             const int r0 = ((bk & 0xFFFF) - t1o + JM) & mask, c0 = (((bk >> 16) & 0xFFFF) - t2o + JM) & mask;
             // the next item's loads are in flight meanwhile (past the chunk: its last item again)
-            idx = item(min(j + 1, j1 - 1));
+            const int jn = min(j + 1, j1 - 1);
+            idx = item(jn);
             bk = base[idx];
             f = fr[idx];
-            v = value(idx);
+            v = value(jn, idx);
             // taps q (l) and J - 1 - q (h) of the two axes, as kb_weights
             auto pair = [&](float fx, float& l, float& h) {
                 const float x = fx - 0.5f, x2 = x * x;
@@ -791,9 +828,15 @@ void grid_tt(const Plan& P, const cpx<T>* y, const cpx<T>* gin, const int32_t* p
         // J = 6 to 8; with five taps the pairs fill three of a quad's lanes, the last for one
         // column (2048^2, 2 10^6 visibilities: 371 -> 375 us)
         quad = P.J >= 6 && P.J <= 8;
-        if (quad)
+        if (quad && perm && stages_values(P)) {
+            // a unit's values: its share of a split tile's five ranges, each rounded up
+            const size_t lds = (size_t)(P.grid_unit + 8) * sizeof(cpx<T>);
             PURIFY_J_DISPATCH(P.J, if constexpr (J_ >= 6) hipLaunchKernelGGL(
-                                       (k_grid_quad<J_, TT, 256>), g, dim3(256), 0, s, y, perm, P.base, fr, kbc, P.gwork,
+                                       (k_grid_quad<J_, TT, 256, true>), g, dim3(256), lds, s, y, perm, P.base, fr, kbc,
+                                       P.gwork, scr, P.gexp, grid, P.K, P.nT));
+        } else if (quad)
+            PURIFY_J_DISPATCH(P.J, if constexpr (J_ >= 6) hipLaunchKernelGGL(
+                                       (k_grid_quad<J_, TT, 256, false>), g, dim3(256), 0, s, y, perm, P.base, fr, kbc, P.gwork,
                                        scr, P.gexp, grid, P.K, P.nT));
     }
     if (!quad)

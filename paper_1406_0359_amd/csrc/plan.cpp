@@ -272,7 +272,6 @@ size_t layout(Plan& P, const purify_plan_desc* d, char* ws) {
     P.base = (int32_t*)carve(M * 4);
     P.frac = carve(2 * M * es);
     P.perm = (int32_t*)carve(M * 4);
-    P.inv = sorts_values(P) ? (int32_t*)carve(M * 4) : nullptr;
     P.tileoff = (int32_t*)carve(((size_t)4 * P.nT * P.nT + 1) * 4);
     P.tilecover = (int32_t*)carve((size_t)P.nT * P.nT * 4);
     // Gridding work units: a tile whose visibility list (own + spill-ins) exceeds
@@ -284,6 +283,7 @@ size_t layout(Plan& P, const purify_plan_desc* d, char* ws) {
     {
         const size_t tiles = (size_t)P.nT * P.nT;
         P.grid_unit = (int)std::max<int64_t>(GRID_UNIT, (2 * (int64_t)M + (int64_t)tiles - 1) / (int64_t)tiles);
+        P.inv = sorts_values(P) ? (int32_t*)carve(M * 4) : nullptr;
         const size_t parts_max = (size_t)(8 * M / P.grid_unit) + 1;
         const size_t split_max = std::min(tiles, (size_t)(4 * M / P.grid_unit) + 1);
         P.gslots = (int)parts_max;

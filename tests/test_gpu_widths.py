@@ -28,6 +28,20 @@ def test_kernel_widths(n, M, prec, J):
     assert rel_l2(to_np(plan.normal(plan.as_vec(x))), op.normal(x)) <= tol
 
 
+@pytest.mark.parametrize("n,M,J", [(32, 1, 6), (64, 1025, 7), (64, 65536, 8), (64, 65537, 8), (512, 700001, 6),
+                                   (1024, 1100003, 8)])
+def test_adjoint_stages_values(n, M, J):
+    """FP32 units of one visibility up to the most that are staged (2048) and one above, split
+    tiles among them.  Uniform cover: at 300 visibilities a cell a quantum is 6e-7 of the largest
+    value, a cell's 256 roundings about 4e-6 of it."""
+    from paper_1406_0359_amd import purify
+    uv = uv_case(M, n, M, 1.0)
+    op = Nufft(n, uv, J)
+    plan = purify.Plan(n, uv, J=J, levels=2, precision="fp32")
+    y = rand_complex(M, 3).astype(np.complex64)
+    assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), op.phi_adj(y)) <= 1e-5
+
+
 @pytest.mark.parametrize("n,M,prec", [(256, 1572864, "fp32"), (256, 1572863, "fp32"), (256, 786433, "fp64")])
 def test_adjoint_sorts_many_values(n, M, prec):
     """Visibility vectors at and below 12 MiB (above it they are sorted before gridding)."""
