@@ -28,6 +28,7 @@
 
 #include "common.h"
 #include "lds_limit.h"
+#include "twiddle.h"
 
 namespace purify {
 
@@ -232,58 +233,6 @@ struct Plan1D {
     }
 };
 
-// FP32 lines of 2048 and more take their inter-pass twiddles from two short tables,
-// W[m] = W[(m >> LB) 2^LB] W[m mod 2^LB] (2^LB + n / 2^LB entries instead of n; one more
-// rounding, well inside FP32 accuracy), so a workgroup's LDS is little more than its line
-// buffers and two workgroups of 4096-point lines fit on a CU (2048^2, 10^6 visibilities:
-// Phi^dagger Phi 378 -> 366 us; at 1024 and below within 2% either way).
-template <typename T, int LOGN>
-constexpr bool twiddles_split() { return sizeof(T) == 4 && LOGN >= 11; }
-template <typename T, int LOGN>
-constexpr int split_lb() { return (LOGN + 1) / 2; }
-// twiddle W[m] = exp(-2 pi i m / n) from the staged table
-template <typename T, int LOGN>
-__device__ __forceinline__ cpx<T> tw_get(const cpx<T>* W, int m) {
-    if constexpr (twiddles_split<T, LOGN>()) {
-        constexpr int LB = split_lb<T, LOGN>(), L = 1 << LB;
-        return W[L + (m >> LB)] * W[m & (L - 1)];
-    } else {
-        return W[m];
-    }
-}
-
-// apply(r, W[r k STEP]), 0 < r < R: the twiddles of one butterfly.  Of split tables a radix-8
-// butterfly takes three values and forms the others as their products (the same operations as
-// the tables' own products, six instead of fourteen LDS reads: as much as the data's exchange),
-// and steps that are multiples of the low table's length need the high table alone.  4096^2
-// column passes 452 -> 431 us (adjoint) and 428 -> 419, row passes 108 -> 107 and 99 -> 98.
-template <typename T, int LOGN, int R, int STEP, typename Fn>
-__device__ __forceinline__ void twiddles(const cpx<T>* W, int k, Fn apply) {
-    if constexpr (twiddles_split<T, LOGN>()) {
-        constexpr int LB = split_lb<T, LOGN>(), L = 1 << LB;
-        auto get = [&](int m) {
-            if constexpr (STEP % L == 0) return W[L + (m >> LB)];
-            else return W[L + (m >> LB)] * W[m & (L - 1)];
-        };
-        if constexpr (R == 8 && STEP % L != 0) {
-            const cpx<T> w1 = get(k * STEP), w2 = get(2 * k * STEP), w4 = get(4 * k * STEP), w3 = w1 * w2;
-            apply(1, w1);
-            apply(2, w2);
-            apply(3, w3);
-            apply(4, w4);
-            apply(5, w4 * w1);
-            apply(6, w4 * w2);
-            apply(7, w4 * w3);
-        } else {
-#pragma unroll
-            for (int r = 1; r < R; ++r) apply(r, get(r * k * STEP));
-        }
-    } else {
-#pragma unroll
-        for (int r = 1; r < R; ++r) apply(r, tw_get<T, LOGN>(W, r * k * STEP));
-    }
-}
-
 // Pass P of NC lines at once (the thread's RMAX registers of each one after another, line buffers `lstep` elements apart):
 // they share the barriers and the twiddles.
 template <typename T, int LOGN, int AX, int P, bool INV, int NC>
@@ -398,10 +347,7 @@ constexpr bool twiddles_in_lds() {
     return twiddles_split<T, LOGN>() || (size_t)(N + 2 * (N + 1)) * 2 * sizeof(T) <= 160 * 1024;
 }
 template <typename T, int LOGN>
-constexpr int table_elems() {
-    if constexpr (twiddles_split<T, LOGN>()) return (1 << split_lb<T, LOGN>()) + (1 << (LOGN - split_lb<T, LOGN>()));
-    else return twiddles_in_lds<T, LOGN>() ? (1 << LOGN) : 0;
-}
+constexpr int table_elems() { return twiddles_in_lds<T, LOGN>() ? twiddle_entries<T, LOGN>() : 0; }
 template <typename T, int LOGN>
 constexpr int cols_per_wg() {
     constexpr int N = 1 << LOGN;
@@ -479,13 +425,8 @@ __device__ __forceinline__ const cpx<T>* mc_stage_tw2(cpx<T>* lines, const cpx<T
 
 template <typename T, int LOGN>
 __device__ __forceinline__ const cpx<T>* stage_twiddles(cpx<T>* Wl, const cpx<T>* __restrict__ tw) {
-    if constexpr (twiddles_split<T, LOGN>()) {
-        constexpr int LB = split_lb<T, LOGN>(), L = 1 << LB;
-        for (int i = threadIdx.x; i < table_elems<T, LOGN>(); i += blockDim.x)
-            Wl[i] = i < L ? tw[i] : tw[(size_t)(i - L) << LB];
-        return Wl;
-    } else if constexpr (twiddles_in_lds<T, LOGN>()) {
-        for (int i = threadIdx.x; i < (1 << LOGN); i += blockDim.x) Wl[i] = tw[i];
+    if constexpr (twiddles_in_lds<T, LOGN>()) {
+        for (int i = threadIdx.x; i < table_elems<T, LOGN>(); i += blockDim.x) Wl[i] = tw[twiddle_entry<T, LOGN>(i)];
         return Wl;
     } else {
         return tw;
