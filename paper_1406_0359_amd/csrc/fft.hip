@@ -364,7 +364,7 @@ constexpr int cols_per_wg() {
 // Long columns (a workgroup's LDS holds only one column's two parity lines, or FP32 lines of
 // 4096 and more) run the kernels that keep CR adjacent columns per thread in registers.
 template <typename T, int LOGN>
-constexpr bool long_cols() { return LOGN >= 11 && (cols_per_wg<T, LOGN>() == 1 || (sizeof(T) == 4 && LOGN >= 12)); }
+constexpr bool long_cols() { return LOGN >= 11 && (cols_per_wg<T, LOGN>() == 1 || twiddles_split<T, LOGN>()); }
 template <typename T, int LOGN>
 constexpr int long_cols_cr() { return sizeof(T) == 8 || Plan1D<T, LOGN, 1>::RMAX >= 16 ? 2 : 4; }
 // Column groups of the stored operator's spectrum: element (k1, k2) at

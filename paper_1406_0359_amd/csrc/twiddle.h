@@ -5,13 +5,14 @@
 
 namespace purify {
 
-// FP32 lines of 2048 and more take their inter-pass twiddles from two short tables,
-// W[m] = W[(m >> LB) 2^LB] W[m mod 2^LB] (2^LB + n / 2^LB entries instead of n; one more
-// rounding, well inside FP32 accuracy), so a workgroup's LDS is little more than its line
-// buffers and two workgroups of 4096-point lines fit on a CU (2048^2, 10^6 visibilities:
-// Phi^dagger Phi 378 -> 366 us; at 1024 and below within 2% either way).
+// FP32 lines of 4096 and more take their inter-pass twiddles from two short tables,
+// W[m] = W[(m >> LB) 2^LB] W[m mod 2^LB] (2^LB + n / 2^LB entries instead of n; a twiddle then
+// carries the roundings of two entries and of their product, RMS 4.1e-8 against 2.1e-8), so a
+// workgroup's LDS is little more than its line buffers and two workgroups fit on a CU.  At 2048
+// the full table fits beside the lines, so its accuracy is kept there (the short tables: 2048^2,
+// 10^6 visibilities, Phi^dagger Phi 378 -> 366 us).
 template <typename T, int LOGN>
-constexpr bool twiddles_split() { return sizeof(T) == 4 && LOGN >= 11; }
+constexpr bool twiddles_split() { return sizeof(T) == 4 && LOGN >= 12; }
 template <typename T, int LOGN>
 constexpr int split_lb() { return (LOGN + 1) / 2; }
 // entries of the staged table, and the full table's entry that sits at place i of it

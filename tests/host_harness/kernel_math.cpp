@@ -26,6 +26,12 @@ void line_twiddles_1024(const cpx<float>* tw, cpx<float>* out) {
     pass<10, 8, 8>(W, out);
     pass<10, 16, 64>(W, out + 7 * 8);
 }
+void line_twiddles_2048(const cpx<float>* tw, cpx<float>* out) {
+    static cpx<float> W[2048];
+    stage<11>(tw, W);
+    pass<11, 16, 32>(W, out);
+    pass<11, 4, 512>(W, out + 15 * 32);
+}
 void line_twiddles_4096(const cpx<float>* tw, cpx<float>* out) {
     static cpx<float> W[4096];
     stage<12>(tw, W);

@@ -29,14 +29,14 @@ def lib(tmp_path_factory):
 
 
 # radix and block length of each pass after the first
-PASSES = {1024: [(8, 8), (16, 64)], 4096: [(8, 8), (8, 64), (8, 512)]}
+PASSES = {1024: [(8, 8), (16, 64)], 2048: [(16, 32), (4, 512)], 4096: [(8, 8), (8, 64), (8, 512)]}
 # A part of a twiddle is below 1 in magnitude, so one rounding moves it by at most h = 2^-25 and,
 # uniform over that, by 2 h / sqrt(12) in RMS; a complex value is sqrt(2) off as much.  A table
 # entry is rounded once.  A product of two entries carries both entries' roundings and two of its
 # own (the product of the imaginary parts, then the multiply-add): at most 2 + 2 = 4 of them in a
 # part, and in RMS sqrt(1 + 1 + 2).
 H = 2.0 ** -25 * np.sqrt(2.0)
-BOUND = {1024: (H, 2 * H / np.sqrt(12.0)), 4096: (4 * H, 4 * H / np.sqrt(12.0))}
+BOUND = {1024: (H, 2 * H / np.sqrt(12.0)), 2048: (H, 2 * H / np.sqrt(12.0)), 4096: (4 * H, 4 * H / np.sqrt(12.0))}
 
 
 @pytest.mark.parametrize("n", sorted(PASSES))
