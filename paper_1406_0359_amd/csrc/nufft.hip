@@ -566,10 +566,10 @@ k_grid(const cpx<T>* __restrict__ y, const cpx<T>* __restrict__ gin, const int32
 
 #undef PURIFY_STAGE_WINDOW
 
-// G^T in FP32 with four lanes a visibility, for widths with three or four tap pairs: k_grid's unit, accumulator and arithmetic (the same sums, bit for bit), but lane q of a quad
-// evaluates taps q and J - 1 - q of both axes -- one even/odd pair each -- and adds those two
-// columns of the footprint, row by row, with the rows' weights times the value broadcast from the
-// quad's lanes.  k_grid is bound by its LDS atomics: with a few visibilities a thread many lanes
+// G^T in FP32 with four lanes a visibility, for widths with three or four tap pairs: k_grid's
+// unit, accumulator and arithmetic, but lane q of a quad evaluates taps q and J - 1 - q of both
+// axes (one polynomial, at x and at -x) and adds those two columns of the footprint, row by row,
+// with the rows' weights times the value broadcast from the quad's lanes.  k_grid is bound by its LDS atomics: with a few visibilities a thread many lanes
 // have none in a round, and 64 lanes' single cells meet in the banks (4096^2: LDS busy 82% of the
 // time, 56% of that with conflicts); here a unit's rounds are full but for the last, and a quad's
 // cells are four neighbours.  256 threads a unit (128, 512: slower).  4096^2, J = 8: G^T 505 -> 430
@@ -685,26 +685,10 @@ k_grid_quad(const cpx<float>* __restrict__ y, const int32_t* __restrict__ perm, 
             bk = base[idx];
             f = fr[idx];
             v = value(jn, idx);
-            // taps q (l) and J - 1 - q (h) of the two axes, as kb_weights
-            auto pair = [&](float fx, float& l, float& h) {
-                const float x = fx - 0.5f, x2 = x * x;
-                float ev = c[NC - 2], od = c[NC - 1];
-#pragma unroll
-                for (int d = NC - 4; d >= 0; d -= 2) {
-                    ev = fmaf(ev, x2, c[d]);
-                    od = fmaf(od, x2, c[d + 1]);
-                }
-                l = fmaf(x, od, ev);
-                h = fmaf(-x, od, ev);
-            };
-            float al, ah, bl, bh;
-            pair(fc.x, al, ah);
-            pair(fc.y, bl, bh);
-            if (2 * q == J - 1) {   // odd widths: the middle tap once
-                al = ah;
-                bl = bh;
-                bh = 0.0f;
-            }
+            float al, ah, bl, bh;   // taps q and J - 1 - q of the two axes
+            kb_pair<float>(c, fc.x - 0.5f, al, ah);
+            kb_pair<float>(c, fc.y - 0.5f, bl, bh);
+            if (2 * q == J - 1) bh = 0.0f;   // odd widths: the middle tap once
             const float sl = al * inv_q, sh = ah * inv_q;
             const float lx = sl * vc.x, ly = sl * vc.y, hx = sh * vc.x, hy = sh * vc.y;
             if (q < NP) {

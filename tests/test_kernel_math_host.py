@@ -9,6 +9,8 @@ import subprocess
 import numpy as np
 import pytest
 
+from oracle.kaiser_bessel import default_beta, kb_kernel
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1406_0359_amd", "csrc")
 HARNESS = os.path.join(ROOT, "tests", "host_harness", "kernel_math.cpp")
@@ -56,3 +58,39 @@ def test_line_twiddles(lib, n):
         assert err.max() <= most * (1 + 1e-6), (radix, ns)
         if ns >= 64:   # enough butterflies for a mean
             assert np.sqrt((err ** 2).mean(0)).max() <= rms, (radix, ns)
+
+
+def _tap_polynomials(J, degree=9):
+    """Coefficients [tap][k] in x = f - 1/2 of psi(f + J/2 - 1 - tap), f in [0, 1)."""
+    out = []
+    for a in range(J):
+        p = np.polynomial.Chebyshev.interpolate(lambda x, a=a: kb_kernel(x + 0.5 * J - 0.5 - a, J, default_beta(J)), degree,
+                                                domain=[-0.5, 0.5])
+        out.append(p.convert(kind=np.polynomial.Polynomial, domain=[-1, 1], window=[-1, 1]).coef)
+    return np.ascontiguousarray(np.array(out, np.float32))
+
+
+def _horner(c, x):
+    """One Horner chain a tap in FP32: a product of two FP32 values is exact in FP64, so an FP64
+    product and sum rounded to FP32 is the fused multiply-add."""
+    acc = np.broadcast_to(c[:, -1].astype(np.float64), (x.size, len(c)))
+    for k in range(c.shape[1] - 2, -1, -1):
+        acc = (acc * x[:, None].astype(np.float64) + c[:, k]).astype(np.float32).astype(np.float64)
+    return acc
+
+
+@pytest.mark.parametrize("fn", ["kb_taps", "kb_tap_pairs"])
+@pytest.mark.parametrize("J", [4, 5, 6, 7, 8])
+def test_kernel_weights(lib, J, fn):
+    """The FP32 Kaiser-Bessel weights are as close to psi as one Horner chain a tap gives them.  Half
+    a percent is for a different rounding of the high terms: one more rounding there reaches a
+    weight times x^4, whose mean square over |x| < 1/2 is 1/2304, against a weight's own two."""
+    f = np.linspace(0, 1, 20001)[:-1].astype(np.float32)
+    c, x = _tap_polynomials(J), f - np.float32(0.5)
+    t = (x.astype(np.float64)[:, None] + 0.5 * J - 0.5) - np.arange(J)[None, :]
+    psi = kb_kernel(t, J, default_beta(J))
+    got = np.zeros((f.size, J), np.float32)
+    ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    getattr(lib, fn)(J, ptr(c), ptr(f), f.size, ptr(got))
+    rms = lambda w: np.sqrt(((w - psi) ** 2).mean())
+    assert rms(got) <= 1.005 * rms(_horner(c, x))
