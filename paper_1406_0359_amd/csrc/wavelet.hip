@@ -289,12 +289,14 @@ struct SynthWin {
 };
 
 // A thread's window elements (lane = window column) into registers: the low rows (the LL block
-// or the axis-1 detail), then the high rows (the two other details), positions past the filter's
-// own clamped to the last one as in k_wav_fwd.  SKIP leaves out loads wholly past it (only where
-// a barrier parts the loads from the stores, or the compiler joins the two blocks), and takes two
-// rows a wave where a row is at most 32 columns (Psi 1024^2 FP32 57.7 -> 56.3 us, 4096^2 629 -> 617,
-// 4096^2 with Db1 and Db2 alone 161 -> 150).  Sides are powers of two, so a row's offset is a
-// shift (64-bit products took as many cycles here as a filter step).
+// or the axis-1 detail), then the high rows (the two other details); rows past the filter's own
+// are clamped to the last one as in k_wav_fwd, and lanes past its columns to the last column (left
+// to run on they read up to thirty more columns a row: 4096^2 FP32 Psi, Db2 alone 111 -> 102 us,
+// all bases 617 -> 607).  SKIP leaves out loads wholly past the rows (only where a barrier parts
+// the loads from the stores, or the compiler joins the two blocks), and takes two rows a wave where
+// a row is at most 32 columns (Psi 1024^2 FP32 57.7 -> 56.3 us, 4096^2 629 -> 617, 4096^2 with Db1
+// and Db2 alone 161 -> 150).  Sides are powers of two, so a row's offset is a shift (64-bit products
+// took as many cycles here as a filter step).
 template <typename T, typename G, bool SKIP>
 __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __restrict__ ab,
                                            const cpx<T>* __restrict__ lls, int lld, int n, int half, int m0, int m1,
@@ -303,7 +305,7 @@ __device__ __forceinline__ void synth_load(SynthWin<T, G>& w, const cpx<T>* __re
     const int s0 = m0 / 2 - F / 2 + 1, s1 = m1 / 2 - F / 2 + 1;   // first window index
     // windows of at most half a wave's lanes: two rows a wave
     const bool narrow = SKIP && G::LW == 64 && 2 * C1 <= 32;
-    const int b = narrow ? tid & 31 : tid % G::LW, a0 = narrow ? tid >> 5 : tid / G::LW;
+    const int b = min(narrow ? tid & 31 : tid % G::LW, 2 * C1 - 1), a0 = narrow ? tid >> 5 : tid / G::LW;
     const int LR = narrow ? 2 * G::LR : G::LR;
     const bool h1 = b >= C1;
     const int i1 = (s1 + (h1 ? b - C1 : b)) & (half - 1);
@@ -661,13 +663,16 @@ void inv_level(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T
 template <typename T, typename G>
 void inv_final_pipe(const Plan& P, const WavArgs& A, const cpx<T>* alpha, const cpx<T>* in, int from_alpha, cpx<T>* x,
                     T scale, hipStream_t s) {
-    // Filters of at most four taps have hardly a halo to share in an L2; once image and coefficients
-    // outgrow the 256 MB last-level cache their tiles go in raster order, all XCDs on one stretch
-    // of memory (4096^2 FP32, Db1 and Db2 150 -> 146 us, Db1 93 -> 87; 2048^2 37.9 -> 40.6 us, and with
-    // all nine bases 4096^2 617 -> 643, so neither of those)
+    // Filters of at most four taps have hardly a halo to share in an L2; where the image and the
+    // coefficients (Dirac's among them) reach the 256 MB of the last-level cache their tiles go in
+    // raster order, all XCDs on one stretch of memory.  XCD ranges and raster, us: 4096^2 FP32 Db1
+    // 94 and 88, Db2 108 and 102, both 153 and 144, Dirac with Db1 109 and 103, with Db2 119 and 112,
+    // with both 166 and 154; FP64 165 and 158, 195 and 184, 277 and 265; 2048^2 FP64 Dirac with both 92
+    // and 85.  2048^2 FP32 Db2 32.4 and 33.4, and with all nine bases 4096^2 617 and 643, so neither
+    // of those.
     int fmax = 0;
     for (int z = 0; z < A.nwav; ++z) fmax = std::max(fmax, A.flen[z]);
-    const int raster = fmax <= 4 && (size_t)(A.nwav + 1) * P.N * sizeof(cpx<T>) >= (size_t)256 << 20;
+    const int raster = fmax <= 4 && (size_t)(P.q + 1) * P.N * sizeof(cpx<T>) >= (size_t)256 << 20;
     hipLaunchKernelGGL((k_wav_inv_final_pipe<T, G>), dim3(P.N / (4 * G::TP0 * G::TP1)), dim3(G::NT), 0, s, alpha, in,
                        from_alpha, x, (const T*)P.filters, A, raster, scale);
 }

@@ -27,3 +27,14 @@ def test_dictionary_edges(n, mask, levels, prec):
     tol = 1e-12 if prec == "fp64" else 1e-5
     assert rel_l2(to_np(plan.psi_adj(plan.as_vec(x))), sa.psi_adj(x)) <= tol
     assert rel_l2(to_np(plan.psi(plan.as_vec(a))), sa.psi(a)) <= tol
+
+
+@pytest.mark.parametrize("n,mask,prec", [(2048, 0x007, "fp64"), (4096, 0x004, "fp32")])
+def test_dictionary_raster_tiles(n, mask, prec):
+    """Short filters where image and coefficients just reach 256 MB (four blocks in FP64, two in FP32):
+    the finest synthesis takes its tiles in raster order."""
+    from paper_1406_0359_amd import purify
+    plan = purify.Plan(n, np.random.default_rng(n).uniform(-3, 3, (50, 2)), dict_mask=mask, levels=2, precision=prec)
+    sa = Sara(n, mask, 2)
+    a = rand_complex((sa.q, n, n), n)
+    assert rel_l2(to_np(plan.psi(plan.as_vec(a))), sa.psi(a)) <= (1e-12 if prec == "fp64" else 1e-5)
