@@ -105,3 +105,20 @@ def test_toeplitz_sdmm_fp32_snr_within_005db_of_fp64_oracle():
                        device=DEV)
     res = plan.sdmm(plan.as_vec(p.y), p.epsilon, max_iter=w.iters, toeplitz=True)
     assert abs(synth.snr_db(p.x_true, to_np(res.x)) - synth.snr_db(p.x_true, ref.x)) < 0.05
+
+
+@pytest.mark.parametrize("n", [2048, 4096])
+def test_toeplitz_fp32_commutes_with_shifts(n):
+    """The stored operator is a convolution, so a shifted image gives the shifted result, whatever
+    the error of the stored spectrum: what is left is the rounding of the transforms (4096: lines
+    of radix 8, two columns at a time).  Sixteen radix-8 passes (two axes, there and back, four a
+    line) of about 7e-8 each (a twiddle 4e-8, its product 3e-8, three additions 4e-8) add up to
+    3e-7, 4e-7 in the difference of two results; held to 1e-6."""
+    M, s = 50021, (3, 5)
+    uv = synth.uv_coverage(M, 2 * n, np.random.default_rng(n), 0.1)
+    plan = purify.Plan(n, uv, J=8, dict_mask=0x100, levels=2, precision="fp32", device=DEV)
+    x = np.zeros((n, n), np.complex64)
+    x[:n // 2, :n // 2] = rand_complex((n // 2, n // 2), 6)
+    a = to_np(plan.normal(plan.as_vec(x), toeplitz=True))
+    b = to_np(plan.normal(plan.as_vec(np.roll(x, s, (0, 1))), toeplitz=True))
+    assert rel_l2(b[s[0]:, s[1]:], a[:n - s[0], :n - s[1]]) <= 1e-6
