@@ -233,11 +233,8 @@ struct Plan1D {
     }
 };
 
-// Pass P of NC lines at once (the thread's RMAX registers of each one after another, line buffers `lstep` elements apart):
-// they share the barriers and the twiddles.
-template <typename T, int LOGN, int AX, int P, bool INV, int NC>
-__device__ __forceinline__ void fft_pass(cpx<T>* v, cpx<T>* line, int lstep, int tl,
-                                         const cpx<T>* W) {
+template <typename T, int LOGN, int AX, int P, bool INV>
+__device__ __forceinline__ void fft_pass(cpx<T>* v, cpx<T>* line, int tl, const cpx<T>* W) {
     using PL = Plan1D<T, LOGN, AX>;
     using Rd = Radices<T, LOGN, AX>;
     constexpr int N = PL::N;
@@ -247,62 +244,45 @@ __device__ __forceinline__ void fft_pass(cpx<T>* v, cpx<T>* line, int lstep, int
     static_assert(!PL::PAD || ((N / R) % 8 == 0 && (NS % 8 == 0 || (NS == 1 && R % 8 == 0))), "padded lines");
     if constexpr (P > 0) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        for (int b = 0; b < NB; ++b) {
+            const int j = PL::at(tl) + PL::span(b * PL::TL);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int j = c * lstep + PL::at(tl) + PL::span(b * PL::TL);
-#pragma unroll
-                for (int r = 0; r < R; ++r) v[c * PL::RMAX + b * R + r] = line[j + r * PL::span(N / R)];
-            }
+            for (int r = 0; r < R; ++r) v[b * R + r] = line[j + r * PL::span(N / R)];
         }
         __syncthreads();
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int j = tl + b * PL::TL;
             const int k = j % NS;
-            auto apply = [&](int r, cpx<T> w) {
+            twiddles<T, LOGN, R, N / (NS * R)>(W, k, [&](int r, cpx<T> w) {
                 if (INV) w.y = -w.y;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) v[c * PL::RMAX + b * R + r] = v[c * PL::RMAX + b * R + r] * w;
-            };
-            twiddles<T, LOGN, R, N / (NS * R)>(W, k, apply);
+                v[b * R + r] = v[b * R + r] * w;
+            });
         }
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) reg_dft<T, R, INV>(v + c * PL::RMAX + b * R);
-    }
+    for (int b = 0; b < NB; ++b) reg_dft<T, R, INV>(v + b * R);
     if constexpr (P < Rd::NP - 1) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        for (int b = 0; b < NB; ++b) {
+            const int j = tl + b * PL::TL;
+            const int k = j % NS;
+            const int o = PL::at((j - k) * R + k);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int j = tl + b * PL::TL;
-                const int k = j % NS;
-                const int o = c * lstep + PL::at((j - k) * R + k);
-#pragma unroll
-                for (int t = 0; t < R; ++t) line[o + (NS == 1 ? PL::at_c(t) : PL::span(t * NS))] = v[c * PL::RMAX + b * R + t];
-            }
+            for (int t = 0; t < R; ++t) line[o + (NS == 1 ? PL::at_c(t) : PL::span(t * NS))] = v[b * R + t];
         }
         __syncthreads();
     }
 }
 
-// Run every pass on this thread's registers; `line` is this line's LDS buffer (NC lines: the
-// buffers are lstep elements apart).
-template <typename T, int LOGN, int AX, bool INV, int NC>
-__device__ __forceinline__ void lines_fft(cpx<T>* v, cpx<T>* line, int lstep, int tl,
-                                          const cpx<T>* W) {
-    using Rd = Radices<T, LOGN, AX>;
-    fft_pass<T, LOGN, AX, 0, INV, NC>(v, line, lstep, tl, W);
-    if constexpr (Rd::NP > 1) fft_pass<T, LOGN, AX, 1, INV, NC>(v, line, lstep, tl, W);
-    if constexpr (Rd::NP > 2) fft_pass<T, LOGN, AX, 2, INV, NC>(v, line, lstep, tl, W);
-    if constexpr (Rd::NP > 3) fft_pass<T, LOGN, AX, 3, INV, NC>(v, line, lstep, tl, W);
-}
+// Run every pass on this thread's registers; `line` is this line's LDS buffer.
 template <typename T, int LOGN, int AX, bool INV>
 __device__ __forceinline__ void line_fft(cpx<T>* v, cpx<T>* line, int tl, const cpx<T>* W) {
-    lines_fft<T, LOGN, AX, INV, 1>(v, line, 0, tl, W);
+    using Rd = Radices<T, LOGN, AX>;
+    fft_pass<T, LOGN, AX, 0, INV>(v, line, tl, W);
+    if constexpr (Rd::NP > 1) fft_pass<T, LOGN, AX, 1, INV>(v, line, tl, W);
+    if constexpr (Rd::NP > 2) fft_pass<T, LOGN, AX, 2, INV>(v, line, tl, W);
+    if constexpr (Rd::NP > 3) fft_pass<T, LOGN, AX, 3, INV>(v, line, tl, W);
 }
 
 template <typename T>
@@ -384,13 +364,12 @@ constexpr int mc_wgs_per_cu() {
     constexpr size_t lines = (size_t)(table_elems<T, LOGN>() + 2 * Plan1D<T, LOGN, 1>::LS) * sizeof(cpx<T>);
     return 2 * Plan1D<T, LOGN, 1>::TL <= 512 && 2 * lines <= 160 * 1024 ? 2 : 1;
 }
-// The long-column kernels transform NC columns at once (2 NC line buffers) and keep the n parity
-// twiddles exp(-pi i j / n) in LDS beside their line buffers where they fit: staged at the start
-// (all loads in flight at once), then read for every column from LDS instead of from global
-// memory once each column's data is in.
-template <typename T, int LOGN, int NC>
+// The long-column kernels keep the n parity twiddles exp(-pi i j / n) in LDS beside their two
+// line buffers where they fit: staged at the start (all loads in flight at once), then read
+// for every column from LDS instead of from global memory once each column's data is in.
+template <typename T, int LOGN>
 constexpr bool mc_tw2_in_lds() {
-    return (size_t)(table_elems<T, LOGN>() + 2 * NC * Plan1D<T, LOGN, 1>::LS + (1 << LOGN)) * sizeof(cpx<T>) <=
+    return (size_t)(table_elems<T, LOGN>() + 2 * Plan1D<T, LOGN, 1>::LS + (1 << LOGN)) * sizeof(cpx<T>) <=
            160 * 1024 / mc_wgs_per_cu<T, LOGN>();
 }
 // waves per SIMD the register allocation of a long-column kernel must allow
@@ -399,19 +378,18 @@ constexpr int mc_waves_per_eu() {
     constexpr int w = mc_wgs_per_cu<T, LOGN>() * 2 * Plan1D<T, LOGN, 1>::TL / 256;
     return w < 1 ? 1 : w;
 }
-template <typename T, int LOGN, int NC>
+template <typename T, int LOGN>
 constexpr size_t mc_lds_bytes() {
-    return (size_t)(table_elems<T, LOGN>() + 2 * NC * Plan1D<T, LOGN, 1>::LS +
-                    (mc_tw2_in_lds<T, LOGN, NC>() ? (1 << LOGN) : 0)) *
+    return (size_t)(table_elems<T, LOGN>() + 2 * Plan1D<T, LOGN, 1>::LS + (mc_tw2_in_lds<T, LOGN>() ? (1 << LOGN) : 0)) *
            sizeof(cpx<T>);
 }
-// stage tw2 after the line buffers (a workgroup of 2 TL threads); returns where to read it
-template <typename T, int LOGN, int NC>
+// stage tw2 after the two line buffers (a workgroup of 2 TL threads); returns where to read it
+template <typename T, int LOGN>
 __device__ __forceinline__ const cpx<T>* mc_stage_tw2(cpx<T>* lines, const cpx<T>* __restrict__ tw2) {
     using PL = Plan1D<T, LOGN, 1>;
-    if constexpr (mc_tw2_in_lds<T, LOGN, NC>()) {
+    if constexpr (mc_tw2_in_lds<T, LOGN>()) {
         constexpr int NQ = PL::RMAX / 2;
-        cpx<T>* t2l = lines + 2 * NC * PL::LS;
+        cpx<T>* t2l = lines + 2 * PL::LS;
         cpx<T> t[NQ];
 #pragma unroll
         for (int k = 0; k < NQ; ++k) t[k] = tw2[threadIdx.x + k * 2 * PL::TL];
@@ -927,7 +905,7 @@ k_fft_cols_fwd_mc(const cpx<T>* __restrict__ tmp, cpx<T>* __restrict__ grid, con
     const int r = threadIdx.x / PL::TL, tl = threadIdx.x % PL::TL;
     cpx<T>* line = base + table_elems<T, LOGN>() + r * PL::LS;
     const int col0 = strip_block(sg) * CR;
-    const cpx<T>* T2 = mc_stage_tw2<T, LOGN, 1>(base + table_elems<T, LOGN>(), tw2);
+    const cpx<T>* T2 = mc_stage_tw2<T, LOGN>(base + table_elems<T, LOGN>(), tw2);
     __syncthreads();
     cpx<T> v[CR][PL::RMAX];
 #pragma unroll
@@ -975,7 +953,7 @@ k_fft_cols_adj_mc(const cpx<T>* __restrict__ grid, cpx<T>* __restrict__ tmp, con
     cpx<T>* line = lines + r * PL::LS;
     const int col0 = strip_block(sg) * CR;
     constexpr int NQ = PL::RMAX / 2;
-    const cpx<T>* T2 = mc_stage_tw2<T, LOGN, 1>(lines, tw2);
+    const cpx<T>* T2 = mc_stage_tw2<T, LOGN>(lines, tw2);
     __syncthreads();
     // The (-1)^k' factor of the input is left out: it shifts each transform by n/2, so the
     // combine reads position j + n/2 (mod n) of the lines instead.  The loads then have no
@@ -1115,12 +1093,10 @@ k_fft_cols_toep(const cpx<T>* in, cpx<T>* out, const T* __restrict__ chat, const
 
 
 // The stored normal operator's column stage for long columns: each thread keeps CR adjacent
-// columns in registers and the workgroup transforms them together, each through line buffers of
-// its own, so that they share barriers and twiddles (4096^2 normal operator 896 -> 848 us against
-// one after the other; the forward and adjoint passes' four columns spilled so), each column with
-// the same arithmetic as k_fft_cols_toep; a column's adjoint output replaces its input in
-// registers and all CR columns are written at the end (in place is safe: every read precedes
-// every write).
+// columns in registers (32-byte runs of a row, as in k_fft_cols_fwd_mc) and the workgroup
+// takes them one after another through the same two line buffers, each column with the same
+// arithmetic as k_fft_cols_toep; a column's adjoint output replaces its input in registers and
+// all CR columns are written at the end (in place is safe: every read precedes every write).
 template <typename T, int LOGN, int CR>
 __global__ void __launch_bounds__((2 * Plan1D<T, LOGN, 1>::TL)) __attribute__((amdgpu_waves_per_eu(mc_waves_per_eu<T, LOGN>())))
 k_fft_cols_toep_mc(const cpx<T>* in, cpx<T>* out, const T* __restrict__ chat, const cpx<T>* __restrict__ tw,
@@ -1134,7 +1110,7 @@ k_fft_cols_toep_mc(const cpx<T>* in, cpx<T>* out, const T* __restrict__ chat, co
     cpx<T>* lines = base + table_elems<T, LOGN>();
     cpx<T>* line = lines + r * PL::LS;
     const int col0 = strip_block(sg) * CR;
-    const cpx<T>* T2 = mc_stage_tw2<T, LOGN, CR>(lines, tw2);
+    const cpx<T>* T2 = mc_stage_tw2<T, LOGN>(lines, tw2);
     __syncthreads();
     cpx<T> v[CR][PL::RMAX];
 #pragma unroll
@@ -1151,46 +1127,34 @@ k_fft_cols_toep_mc(const cpx<T>* in, cpx<T>* out, const T* __restrict__ chat, co
             for (int cc = 0; cc < CR; ++cc) v[cc][i] = v[cc][i] * t;
         }
     }
-    lines_fft<T, LOGN, 1, false, CR>(v[0], line, 2 * PL::LS, tl, W);
-    // frequency k1 = 2k' + r holds (-1)^k' i^r v; the adjoint reads (-1)^k' times its input
 #pragma unroll
-    for (int c = 0; c < CR; ++c) {
+    for (int cc = 0; cc < CR; ++cc) {
+        line_fft<T, LOGN, 1, false>(v[cc], line, tl, W);
+        // frequency k1 = 2k' + r holds (-1)^k' i^r v; the adjoint reads (-1)^k' times its input
 #pragma unroll
         for (int i = 0; i < PL::RMAX; ++i) {
             const int kp = PL::out_pos(tl, i);
-            cpx<T> o = chat[((size_t)(col0 / CR) * K + 2 * kp + r) * CR + c] * v[c][i];
-            v[c][i] = r ? mul_i(o) : o;
+            cpx<T> o = chat[((size_t)(col0 / CR) * K + 2 * kp + r) * CR + cc] * v[cc][i];
+            v[cc][i] = r ? mul_i(o) : o;
         }
-    }
-    __syncthreads();
+        __syncthreads();
 #pragma unroll
-    for (int c = 0; c < CR; ++c) {
+        for (int i = 0; i < PL::RMAX; ++i) line[PL::out_at(tl, i)] = v[cc][i];
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PL::RMAX; ++i) line[c * 2 * PL::LS + PL::out_at(tl, i)] = v[c][i];
-    }
-    __syncthreads();
+        for (int i = 0; i < PL::RMAX; ++i) v[cc][i] = line[PL::in_at(tl, i)];
+        __syncthreads();
+        line_fft<T, LOGN, 1, true>(v[cc], line, tl, W);
+        __syncthreads();
 #pragma unroll
-    for (int c = 0; c < CR; ++c) {
-#pragma unroll
-        for (int i = 0; i < PL::RMAX; ++i) v[c][i] = line[c * 2 * PL::LS + PL::in_at(tl, i)];
-    }
-    __syncthreads();
-    lines_fft<T, LOGN, 1, true, CR>(v[0], line, 2 * PL::LS, tl, W);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CR; ++c) {
-#pragma unroll
-        for (int i = 0; i < PL::RMAX; ++i) line[c * 2 * PL::LS + PL::out_at(tl, i)] = v[c][i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CR; ++c) {
-        const cpx<T>* l = lines + c * 2 * PL::LS;
+        for (int i = 0; i < PL::RMAX; ++i) line[PL::out_at(tl, i)] = v[cc][i];
+        __syncthreads();
 #pragma unroll
         for (int q = 0; q < PL::RMAX / 2; ++q) {
             const int j = r + 2 * tl + q * 2 * PL::TL, a = PL::at(r + 2 * tl) + PL::span(q * 2 * PL::TL);
-            v[c][q] = l[a] + mul_mi(mulc(l[PL::LS + a], T2[j]));
+            v[cc][q] = lines[a] + mul_mi(mulc(lines[PL::LS + a], T2[j]));
         }
+        __syncthreads();   // the next column reuses the lines
     }
 #pragma unroll
     for (int q = 0; q < PL::RMAX / 2; ++q) {
@@ -1361,7 +1325,7 @@ void cols_fwd_impl(const Plan& P, const cpx<T>* tmp, cpx<T>* grid, hipStream_t s
     const size_t lds = lds_bytes<T, LOGN, 1>(2 * C);
     if constexpr (long_cols<T, LOGN>()) {   // long columns: CR columns per thread in registers
         constexpr int CR = long_cols_cr<T, LOGN>();
-        const size_t lds1 = mc_lds_bytes<T, LOGN, 1>();
+        const size_t lds1 = mc_lds_bytes<T, LOGN>();
         // each XCD takes one contiguous range of column groups (sg = 0), so the groups that
         // share 128-byte lines run on one L2 at about the same time (the adjoint 559 -> 506 us
         // at n = 4096 against the gridding-strip order)
@@ -1384,7 +1348,7 @@ void cols_adj_impl(const Plan& P, const cpx<T>* grid, cpx<T>* tmp, hipStream_t s
     const size_t lds = lds_bytes<T, LOGN, 1>(2 * C);
     if constexpr (long_cols<T, LOGN>()) {
         constexpr int CR = long_cols_cr<T, LOGN>();
-        const size_t lds1 = mc_lds_bytes<T, LOGN, 1>();
+        const size_t lds1 = mc_lds_bytes<T, LOGN>();
         auto f = k_fft_cols_adj_mc<T, LOGN, CR>;
         set_lds_limit(f, lds1);
         hipLaunchKernelGGL(f, dim3(2 * N / CR), dim3(2 * Plan1D<T, LOGN, 1>::TL), lds1, s, grid, tmp,
@@ -1404,7 +1368,7 @@ void cols_toep_impl(const Plan& P, const cpx<T>* in, cpx<T>* out, hipStream_t s)
     const size_t lds = lds_bytes<T, LOGN, 1>(2 * C);
     if constexpr (toep_mc<T, LOGN>()) {
         constexpr int CR = toep_group<T, LOGN>();   // columns per thread, in registers
-        const size_t lds1 = mc_lds_bytes<T, LOGN, CR>();
+        const size_t lds1 = mc_lds_bytes<T, LOGN>();
         auto f = k_fft_cols_toep_mc<T, LOGN, CR>;
         set_lds_limit(f, lds1);
         hipLaunchKernelGGL(f, dim3(2 * N / CR), dim3(2 * Plan1D<T, LOGN, 1>::TL), lds1, s, in, out,

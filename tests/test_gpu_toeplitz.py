@@ -111,7 +111,7 @@ def test_toeplitz_sdmm_fp32_snr_within_005db_of_fp64_oracle():
 def test_toeplitz_fp32_commutes_with_shifts(n):
     """The stored operator is a convolution, so a shifted image gives the shifted result, whatever
     the error of the stored spectrum: what is left is the rounding of the transforms (4096: lines
-    of radix 8, two columns at a time).  Sixteen radix-8 passes (two axes, there and back, four a
+    of radix 8, two columns a thread).  Sixteen radix-8 passes (two axes, there and back, four a
     line) of about 7e-8 each (a twiddle 4e-8, its product 3e-8, three additions 4e-8) add up to
     3e-7, 4e-7 in the difference of two results; held to 1e-6."""
     M, s = 50021, (3, 5)
