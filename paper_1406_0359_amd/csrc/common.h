@@ -197,7 +197,8 @@ struct Plan {
 };
 
 // FP32 gridding of values in caller order by k_grid_quad keeps a work unit's values in LDS (its
-// figures are there), up to 2048 values: with 16 KB more still five workgroups of 32 x 32 tiles a CU.
+// figures are there), up to 2048 values: with 16 KB more still five workgroups of 32 x 32 tiles a
+// CU, four at J = 8.
 inline bool stages_values(const Plan& P) {
     return P.precision == PURIFY_FP32 && P.J >= 6 && P.J <= 8 && P.grid_unit <= 2048;
 }

@@ -311,8 +311,8 @@ __device__ __forceinline__ int strip_block(int sg) {
 // a line are separate thread groups.  Row passes: B rows per workgroup (64-128 threads).
 // Column passes: C adjacent columns (contiguous runs of C elements), at most 1024 threads,
 // at least 256 workgroups (a CU each; with half as many, 512^2 FP64 Phi^dagger Phi took 57 us
-// instead of 52, FP32 51.9 instead of 50.0, 256^2 FP64 Phi^dagger 16.3 instead of 16.0), and LDS
-// (2C lines + twiddle table) within 160 KB.
+// instead of 52, FP32 51.9 instead of 50.0, 256^2 FP64 Phi^dagger 16.3 instead of 16.0) or, below
+// 128-point lines, one for each of the 2n columns, and LDS (2C lines + twiddle table) within 160 KB.
 template <typename T, int LOGN>
 constexpr int rows_per_wg() {
     constexpr int tl = Plan1D<T, LOGN, 0>::TL;

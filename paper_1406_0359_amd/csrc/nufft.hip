@@ -569,17 +569,18 @@ k_grid(const cpx<T>* __restrict__ y, const cpx<T>* __restrict__ gin, const int32
 // G^T in FP32 with four lanes a visibility, for widths with three or four tap pairs: k_grid's
 // unit, accumulator and arithmetic, but lane q of a quad evaluates taps q and J - 1 - q of both
 // axes (one polynomial, at x and at -x) and adds those two columns of the footprint, row by row,
-// with the rows' weights times the value broadcast from the quad's lanes.  k_grid is bound by its LDS atomics: with a few visibilities a thread many lanes
-// have none in a round, and 64 lanes' single cells meet in the banks (4096^2: LDS busy 82% of the
-// time, 56% of that with conflicts); here a unit's rounds are full but for the last, and a quad's
-// cells are four neighbours.  256 threads a unit (128, 512: slower).  4096^2, J = 8: G^T 505 -> 430
-// us (Phi^dagger Phi 1710 -> 1640), 512^2, J = 7 49.4 -> 46.5, 1024^2, J = 6 (three lanes in four)
-// Phi^dagger 115 -> 113.
+// with the rows' weights times the value broadcast from the quad's lanes.  k_grid is bound by its
+// LDS atomics: with a few visibilities a thread many lanes have none in a round, and 64 lanes'
+// single cells meet in the banks; here a unit's rounds are full but for the last, and a quad's
+// cells are four neighbours.  256 threads a unit (128, 512: slower).  k_grid and this, us:
+// Phi^dagger Phi at 4096^2, J = 8 1752 and 1702, 512^2, J = 7 50.0 and 47.0, 1024^2, J = 6 (three
+// lanes in four) 134.4 and 133.7.
 // STAGE (values in caller order): the pass for the largest component keeps the unit's values in
 // LDS, four loads a thread in flight, so that each is read once, not twice, from its random place
-// and not in the chain of the additions: Phi^dagger 1024^2 FP32, J = 6, 2 M visibilities (sorted
-// by a pass of its own before) 114 -> 101 us, 1 M 76.9 -> 64.9, 2048^2 with 4 M 286 -> 267, 256^2 with
-// 60000 19.1 -> 16.8.  Values in sorted order gain nothing by it (4096^2 G^T G 1646 -> 1679 us).
+// and not in the chain of the additions.  Without (vectors from 12 MiB then sorted by a pass of
+// their own) and with it, Phi^dagger in FP32, J = 6, us: 1024^2 with 2 M visibilities 114.5 and
+// 100.5, with 1 M 76.6 and 66.8, 2048^2 with 4 M 294 and 274, 256^2 with 60000 19.5 and 17.2 (k_grid
+// 16.7).  Values in sorted order gain nothing by it (4096^2 G^T G 1646 -> 1679).
 typedef unsigned long long u64;
 
 // lane n of each quad to the quad

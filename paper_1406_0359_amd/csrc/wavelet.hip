@@ -514,7 +514,7 @@ k_wav_inv_final(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ lli
 // its second step, so the loads have both steps to arrive.  The sums over the bases stay in
 // registers.
 // Bound by the windows' loads (1.5 times the coefficients, the halos from L2): 1024^2 FP32 whole
-// synthesis 75 -> 56 us, 4096^2 789 -> 617 us, 1024^2 FP64 195 -> 91 us.
+// synthesis 75 -> 56 us, 4096^2 789 -> 607 us, 1024^2 FP64 195 -> 91 us.
 template <typename T, typename G>
 __global__ void __launch_bounds__(G::NT)
 k_wav_inv_final_pipe(const cpx<T>* __restrict__ alpha, const cpx<T>* __restrict__ llin, int ll_from_alpha,
