@@ -91,10 +91,16 @@ KERNEL_NAME = {
     "fft_rows": "k_fft_rows_fwd", "fft_cols": "k_fft_cols_fwd", "degrid": "k_degrid",
     "grid": "k_grid", "gtg": "k_grid (G^T G)", "ifft_cols": "k_fft_cols_adj", "ifft_rows": "k_fft_rows_adj",
 }
-# where a workload's stage runs other kernels: FP32 grids from 1024^2 apply G^T G as G then
-# G^T (two launches; the stage's algorithmic bytes stay those of G^T G)
-KERNEL_NAME_BY_WORKLOAD = {(w, "gtg"): "k_degrid_tiles + k_grid (G^T G as G then G^T)"
-                           for w in ("sara1024", "sara4096")}
+# where a workload's stage runs other kernels: FP32 gridding with 6 to 8 taps takes four lanes a
+# visibility, and FP32 grids from 1024^2 apply G^T G as G then G^T (two launches; the stage's
+# algorithmic bytes stay those of G^T G)
+KERNEL_NAME_BY_WORKLOAD = {(w, st): name for w in ("sara1024", "sara4096") for st, name in (
+    ("degrid", "k_degrid_tiles"), ("grid", "k_grid_quad"),
+    ("gtg", "k_degrid_tiles + k_grid_quad (G^T G as G then G^T)"))}
+
+
+# what phi_gvis_s and phi_adj_gvis_s count
+VIS_ORDER = "stages on the plan's sorted visibilities; purify_phi and purify_phi_adj also permute to and from caller order"
 
 
 def kernel_name(stage: str, workload: str) -> str:
@@ -200,6 +206,7 @@ def precision_form(torch, purify, synth, solve_iters: int) -> dict:
         "workload": "sara1024 FP32 (n=1024, M=2097152, SARA 9 bases, L=4, J=6)",
         "phi_gvis_s": w.M / (st["phi"]["ms"] * 1e-3) / 1e9,
         "phi_adj_gvis_s": w.M / (st["phi_adj"]["ms"] * 1e-3) / 1e9,
+        "phi_order": VIS_ORDER,
         "psi_adj_GBs": st["psi_adj"]["GBs"], "psi_GBs": st["psi"]["GBs"],
         "sdmm_iters_s_incl_setup": solve_iters / dt,
         "solve_iters": solve_iters, "stages": st,
@@ -388,6 +395,7 @@ def large_solve(torch, purify, synth, iters: int, background: int) -> dict:
         "objective_rel_change_last": abs(r.history[-1, 0] - r.history[-2, 0]) / r.history[-1, 0],
         "phi_gvis_s": w.M / (st["phi"]["ms"] * 1e-3) / 1e9,
         "phi_adj_gvis_s": w.M / (st["phi_adj"]["ms"] * 1e-3) / 1e9,
+        "phi_order": VIS_ORDER,
         "psi_adj_GBs": st["psi_adj"]["GBs"], "psi_GBs": st["psi"]["GBs"],
         "host_inputs_s": t_inputs, "plan_s": t_plan, "nu_s": t_nu, "stages": st,
         "roofline": dominant_roofline(st, w.cg_iters, "sara4096"),

@@ -77,3 +77,12 @@ def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(os.path.dirname(bench.__file__), "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr
+
+
+def test_kernel_names_of_the_fp32_workloads():
+    """FP32 gridding with 6 (1024^2) and 8 taps (4096^2) runs k_grid_quad, 256^2 FP64 runs k_grid."""
+    for w in ("sara1024", "sara4096"):
+        assert bench.kernel_name("grid", w) == "k_grid_quad"
+        assert bench.kernel_name("degrid", w) == "k_degrid_tiles"
+        assert bench.kernel_name("gtg", w) == "k_degrid_tiles + k_grid_quad (G^T G as G then G^T)"
+    assert bench.kernel_name("gtg", "sara256") == "k_grid (G^T G)"
