@@ -309,10 +309,11 @@ __device__ __forceinline__ int strip_block(int sg) {
 
 // Workgroup shapes.  Each n-point line transform uses TL threads; the two output parities of
 // a line are separate thread groups.  Row passes: B rows per workgroup (64-128 threads).
-// Column passes: C adjacent columns (contiguous runs of C elements), at most 1024 threads,
-// at least 256 workgroups (a CU each; with half as many, 512^2 FP64 Phi^dagger Phi took 57 us
-// instead of 52, FP32 51.9 instead of 50.0, 256^2 FP64 Phi^dagger 16.3 instead of 16.0) or, below
-// 128-point lines, one for each of the 2n columns, and LDS (2C lines + twiddle table) within 160 KB.
+// Column passes: C adjacent columns (contiguous runs of C elements), at most 1024 threads, LDS
+// (2C lines + twiddle table) within 160 KB, and 256 workgroups, a CU each, where runs of 32 bytes
+// leave as many (128 workgroups and 256, Phi^dagger Phi: 512^2 FP64 68 and 63 us, FP32 46.2 and 44.4,
+// 256^2 FP64 34.4 and 33.8); else at least ~128 (256^2 FP32 30.4 and 30.7, 128^2 FP64 29.7 and 30.6,
+// FP32 25.7 and 26.3).
 template <typename T, int LOGN>
 constexpr int rows_per_wg() {
     constexpr int tl = Plan1D<T, LOGN, 0>::TL;
@@ -333,7 +334,8 @@ constexpr int cols_per_wg() {
     constexpr int N = 1 << LOGN;
     constexpr int tl = Plan1D<T, LOGN, 1>::TL;
     int c = 512 / tl;
-    if (c > (2 * N) / 256) c = (2 * N) / 256;
+    const int full = (2 * N) / 256, cap = full * 2 * sizeof(T) >= 32 ? full : (4 * N) / 256;
+    if (c > cap) c = cap;
     if (c > 8) c = 8;
     if (c < 1) c = 1;
     const int tab = table_elems<T, LOGN>();
