@@ -205,9 +205,13 @@ inline bool stages_values(const Plan& P) {
 // Elsewhere the adjoint puts values in caller order into sorted order first where they outgrow the
 // caches: a visibility's value is read once or twice for every tile that it reaches, and random 8-
 // or 16-byte reads then fetch a line each (16.8 MB in FP32, 1024^2, before values were staged:
-// Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between).
+// Phi^dagger 165 -> 116 us; 16 MB in FP64 142 -> 134; 8 MB 190 -> 197, so the line is between).  In
+// FP64 with eight taps the LDS additions of a visibility take longer than its reads, and the pass
+// only adds to them (1024^2, 2.15 M visibilities: 272 us without it and 285 with, seven taps 261
+// and 243); with more it changes nothing (nine: 546 both).
 inline bool sorts_values(const Plan& P) {
-    return !stages_values(P) && (size_t)P.M * P.elem >= (size_t)12 << 20;
+    if (stages_values(P) || (P.precision == PURIFY_FP64 && P.J >= 8)) return false;
+    return (size_t)P.M * P.elem >= (size_t)12 << 20;
 }
 
 // ---------------------------------------------------------------------------------------

@@ -71,3 +71,14 @@ def test_fp32_lines_of_2048_and_4096():
     normal = op.normal(x)
     assert rel_l2(to_np(plan.normal(plan.as_vec(x))), normal) <= 1e-5
     assert rel_l2(to_np(plan.normal(plan.as_vec(x), toeplitz=True)), normal) <= 1e-4
+
+
+@pytest.mark.parametrize("J", [7, 8])
+def test_adjoint_fp64_many_values(J):
+    """FP64 vectors past 12 MiB: sorted before gridding with seven taps, not with eight."""
+    from paper_1406_0359_amd import purify
+    n, M = 256, 800003
+    uv = uv_case(M, n, M, 0.5)
+    plan = purify.Plan(n, uv, J=J, levels=2, precision="fp64")
+    y = rand_complex(M, 3)
+    assert rel_l2(to_np(plan.phi_adj(plan.as_vec(y))), Nufft(n, uv, J).phi_adj(y)) <= 1e-12
